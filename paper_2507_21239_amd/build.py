@@ -3,8 +3,10 @@
 hipcc cross-compiles without a GPU.  Flags: -O3, no FP contraction (the FP64
 path keeps the operation order of its formulas; FP32 code asks for fused
 multiply-adds explicitly where it wants them), packed FP32 instructions
-disabled.  collide_ilp.hip (the batched kernel of the mixed form without the
-composition mix) is also scheduled for instruction-level parallelism.
+disabled.  collide_ilp.hip and collide_ilp3.hip (the batched kernels of the
+mixed form's common path) are also scheduled for instruction-level parallelism;
+the other collision kernels and collide_ilp3.hip sink instructions into the
+loops where they are used rather than spill their results.
 """
 from __future__ import annotations
 
@@ -18,10 +20,14 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libmcd.so")
-SOURCES = ["capi.hip", "collide.hip", "collide_ilp.hip", "binning.hip", "plan.hip", "transport.hip",
+SOURCES = ["collide_batched.hip", "collide_batched_prob.hip", "collide_ilp.hip", "collide_ilp3.hip",
+           "collide_plain.hip", "collide_plain_prob.hip", "capi.hip", "collide.hip", "binning.hip", "plan.hip", "transport.hip",
            "diagnostics.hip", "noalloc.hip"]
 # per-file flags on top of CFLAGS
-EXTRA = {"collide_ilp.hip": ["-mllvm", "--amdgpu-sched-strategy=max-ilp"]}
+ILP = ["-mllvm", "--amdgpu-sched-strategy=max-ilp"]
+SINK = ["-mllvm", "-sink-insts-to-avoid-spills=1"]
+EXTRA = {"collide_ilp.hip": ILP, "collide_ilp3.hip": ILP + SINK, "collide_batched.hip": SINK,
+         "collide_batched_prob.hip": SINK, "collide_plain.hip": SINK, "collide_plain_prob.hip": SINK}
 ARCH = os.environ.get("MCD_ARCH", "gfx950")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -48,7 +54,7 @@ def _compile(src: str, verbose: bool) -> str:
 
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
-    with cf.ThreadPoolExecutor(max_workers=min(4, os.cpu_count() or 1)) as ex:
+    with cf.ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as ex:
         objs = list(ex.map(lambda s: _compile(s, verbose), SOURCES))
     tmp = LIB + ".tmp"
     cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs]

@@ -26,9 +26,7 @@
 // composition mix and the event log only in the variant launched for runs
 // that use them.
 //
-// The cell body and the kernel templates; collide.hip launches them, and
-// collide_ilp.hip holds the one instantiation built with a different
-// instruction schedule.
+// The cell body and the kernel templates; collide_launch.hpp launches them.
 #pragma once
 
 #include <algorithm>
@@ -44,15 +42,16 @@ namespace mcd {
 template <typename RT>
 struct RecStore;
 
+// FP32: the three 16-byte words of a record lie together, so that one address
+// serves all of a lane's slots (the slot and the word are immediate offsets);
+// at a stride of 48 bytes the 16-byte reads of 16 consecutive lanes fall on
+// distinct banks
 template <>
 struct RecStore<float> {
-  float4 *A;  // im, a, St, h
-  float4 *B;  // q1, vr, vp, vz
-  float4 *C;  // nd, m, ist, Mn
-  __device__ RecStore(char *base, int cap)
-      : A((float4 *)base), B((float4 *)base + cap), C((float4 *)base + 2 * cap) {}
+  float4 *D;  // per slot: (im, a, St, h) (q1, vr, vp, vz) (nd, m, ist, Mn)
+  __device__ RecStore(char *base, int) : D((float4 *)base) {}
   __device__ Rec<float> load(int s) const {
-    const float4 a = A[s], b = B[s], c = C[s];
+    const float4 a = D[3 * s], b = D[3 * s + 1], c = D[3 * s + 2];
     Rec<float> r;
     r.im = a.x; r.a = a.y; r.St = a.z; r.h = a.w;
     r.q1 = b.x; r.vr = b.y; r.vp = b.z; r.vz = b.w;
@@ -60,9 +59,9 @@ struct RecStore<float> {
     return r;
   }
   __device__ void store(int s, const Rec<float> &r) const {
-    A[s] = make_float4(r.im, r.a, r.St, r.h);
-    B[s] = make_float4(r.q1, r.vr, r.vp, r.vz);
-    C[s] = make_float4(r.nd, r.m, r.ist, r.Mn);
+    D[3 * s] = make_float4(r.im, r.a, r.St, r.h);
+    D[3 * s + 1] = make_float4(r.q1, r.vr, r.vp, r.vz);
+    D[3 * s + 2] = make_float4(r.nd, r.m, r.ist, r.Mn);
   }
 };
 
@@ -148,7 +147,7 @@ __device__ inline void build_rows_pairwise(const RecStore<float> &R, const PairC
     for (int J = I; J < KMAX; ++J) {
       if (J < K) {
         float dv, rxy, ryx;
-        pair_rates_all(pc, mine[I], mine[J], dv, rxy, ryx);
+        pair_rates_all<true>(pc, mine[I], mine[J], dv, rxy, ryx);
         acc[I] += rxy;
         if (J != I) acc[J] += ryx;
       }
@@ -168,7 +167,7 @@ __device__ inline void build_rows_pairwise(const RecStore<float> &R, const PairC
       for (int J = 0; J < KMAX; ++J) {
         if (I < K && J < K) {
           float dv, rxy, ryx;
-          pair_rates_all(pc, mine[I], pr[J], dv, rxy, ryx);
+          pair_rates_all<true>(pc, mine[I], pr[J], dv, rxy, ryx);
           acc[I] += take ? rxy : 0.0f;
           pacc[J] += take ? ryx : 0.0f;
         }
@@ -216,7 +215,7 @@ __device__ inline void build_rows_pairwise_team(const RecStore<float> &R, const 
     for (int J = I; J < KMAX; ++J) {
       if (J < K) {
         float dv, rxy, ryx;
-        pair_rates_all(pc, mine[I], mine[J], dv, rxy, ryx);
+        pair_rates_all<true>(pc, mine[I], mine[J], dv, rxy, ryx);
         acc[I] += rxy;
         if (J != I) acc[J] += ryx;
       }
@@ -237,7 +236,7 @@ __device__ inline void build_rows_pairwise_team(const RecStore<float> &R, const 
       for (int J = 0; J < KMAX; ++J) {
         if (I < K && J < K) {
           float dv, rxy, ryx;
-          pair_rates_all(pc, mine[I], pr[J], dv, rxy, ryx);
+          pair_rates_all<true>(pc, mine[I], pr[J], dv, rxy, ryx);
           acc[I] += take ? rxy : 0.0f;
           pacc[J] += take ? ryx : 0.0f;
         }
@@ -273,7 +272,7 @@ __device__ inline void build_rows_pairwise_team(const RecStore<float> &R, const 
         for (int J = 0; J < KMAX; ++J) {
           if (I < K && J < K) {
             float dv, rxy, ryx;
-            pair_rates_all(pc, mine[I], pr[J], dv, rxy, ryx);
+            pair_rates_all<true>(pc, mine[I], pr[J], dv, rxy, ryx);
             acc[I] += rxy;
             pacc[J] += ryx;
           }
@@ -306,84 +305,58 @@ __device__ inline void build_rows_pairwise_team(const RecStore<float> &R, const 
 }
 
 // ---------------------------------------------------------------------------
-// team: nw waves of one workgroup, runtime size
+// team: the NW waves (1 or 4) that process a cell
 // ---------------------------------------------------------------------------
-struct Team {
-  int nw, wave, lane, tl;
-  TeamScratch *S;
-  int phase;
-  __device__ void sync() const {
-    if (nw > 1)
-      block_lds_sync();
-    else
-      wave_lds_sync();
-  }
-  // the four wave totals of exchange slot k (two 16-byte LDS reads)
-  __device__ void totals4(int k, double t[4]) const {
-    const double2 a = ((const double2 *)S->tot[phase])[2 * k];
-    const double2 b = ((const double2 *)S->tot[phase])[2 * k + 1];
-    t[0] = a.x;
-    t[1] = a.y;
-    t[2] = b.x;
-    t[3] = b.y;
-  }
-  // team-inclusive prefix of x over team lanes; total on every lane.  Teams
-  // have one wave or four; the offset and total add the wave totals in wave
-  // order
-  __device__ double scan(double x, double &total) {
-    const double inc = wave_incl_scan(x);
-    const double wt = readlane_d(inc, 63);
-    if (nw == 1) {
-      total = wt;
-      return inc;
-    }
-    phase ^= 1;
-    if (lane == 63) S->tot[phase][wave] = wt;
+template <int NW>
+__device__ inline void team_sync() {
+  if constexpr (NW > 1)
     block_lds_sync();
-    double t[4];
-    totals4(0, t);
-    double off = 0.0, tot = 0.0;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      if (w < wave) off += t[w];
-      tot += t[w];
+  else
+    wave_lds_sync();
+}
+
+// Team-inclusive prefix of x over the team lanes and its total.  Teams of
+// four waves exchange their totals through `slot` (one barrier); p[w] is then
+// the prefix of the waves' totals up to wave w, added in wave order.
+// With TWO, y is summed too: over each wave in its own precision (BT), then in
+// FP64 over the waves, in the same exchange.
+// A slot may be written again only after another barrier of the team.
+template <int NW, bool TWO, typename BT>
+__device__ __forceinline__ double team_scan(double x, BT y, int wave, int lane, double *slot, double p[4],
+                                   double &tot_x, double &tot_y) {
+  double inc = x;
+  double wy = 0.0;
+  if constexpr (TWO) {
+    wave_incl_scan2(inc, y);
+    wy = (double)readlane_t(y, 63);
+  } else {
+    inc = wave_incl_scan(inc);
+  }
+  const double wx = readlane_d(inc, 63);
+  if constexpr (NW == 1) {
+    tot_x = wx;
+    if (TWO) tot_y = wy;
+    return inc;
+  } else {
+    if (lane == 63) {
+      slot[wave] = wx;
+      if (TWO) slot[4 + wave] = wy;
     }
-    total = tot;
+    block_lds_sync();
+    const double2 a = ((const double2 *)slot)[0], b = ((const double2 *)slot)[1];
+    p[0] = a.x;
+    p[1] = p[0] + a.y;
+    p[2] = p[1] + b.x;
+    p[3] = p[2] + b.y;
+    tot_x = p[3];
+    if (TWO) {
+      const double2 c = ((const double2 *)slot)[2], d = ((const double2 *)slot)[3];
+      tot_y = ((c.x + c.y) + d.x) + d.y;
+    }
+    const double off = wave == 0 ? 0.0 : (wave == 1 ? p[0] : (wave == 2 ? p[1] : p[2]));
     return off + inc;
   }
-  // team-inclusive prefix of a plus the totals of a and b (one exchange); b
-  // is summed over each wave in its own precision (BT), then in FP64
-  template <typename BT>
-  __device__ double scan2(double a, BT b, double &tot_a, double &tot_b) {
-    const double ia = wave_incl_scan(a);
-    const BT ib = wave_incl_scan(b);
-    const double wa = readlane_d(ia, 63), wb = (double)readlane_t(ib, 63);
-    if (nw == 1) {
-      tot_a = wa;
-      tot_b = wb;
-      return ia;
-    }
-    phase ^= 1;
-    if (lane == 63) {
-      S->tot[phase][wave] = wa;
-      S->tot[phase][4 + wave] = wb;
-    }
-    block_lds_sync();
-    double ta4[4], tb4[4];
-    totals4(0, ta4);
-    totals4(1, tb4);
-    double off = 0.0, ta = 0.0, tb = 0.0;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      if (w < wave) off += ta4[w];
-      ta += ta4[w];
-      tb += tb4[w];
-    }
-    tot_a = ta;
-    tot_b = tb;
-    return off + ia;
-  }
-};
+}
 
 // particle state after a collision: FP64 formulas for the FP64 path, the
 // FP32 formulas with per-cell FP32 factors for the mixed path
@@ -391,16 +364,16 @@ template <typename RT>
 struct RecAfter;
 template <>
 struct RecAfter<double> {
-  __device__ static Rec<double> get(const Model &P, const TeamScratch *S, double m, double M,
-                                    double) {
+  __device__ static Rec<double> get(const Model &P, const TeamScratch *S, const CellF &, double m,
+                                    double M, double) {
     return make_rec<double>(P, S->gas, m, M, 1.0);
   }
 };
 template <>
 struct RecAfter<float> {
-  __device__ static Rec<float> get(const Model &, const TeamScratch *S, double m, double,
-                                   float Mn) {
-    return make_rec_f(S->cf, m, Mn);
+  __device__ static Rec<float> get(const Model &, const TeamScratch *, const CellF &cf, double m,
+                                   double, float Mn) {
+    return make_rec_f(cf, m, Mn);
   }
 };
 
@@ -408,152 +381,192 @@ struct RecAfter<float> {
 // selection: the first slot whose cumulative value exceeds a target
 // ---------------------------------------------------------------------------
 // Search inside one wave.  v[] are the lane's K values in canonical order,
-// part their sum, incl the team-inclusive prefix of part.  The chosen lane is
-// the first with incl > target and a nonzero partial (the team prefix is not
-// exactly monotone under rounding), else the wave's last lane with a nonzero
-// partial; inside it, the first slot whose running sum exceeds the target,
-// else its last nonzero slot.  Fills c (team lane, slot, payloads a0[q],
-// a1[q], ai[q], and whether a lane passed the target) uniformly over the
-// wave; false if no lane of the wave has a nonzero partial.
-template <int KMAX, typename VT, typename PT>
-__device__ inline bool wave_pick(int wave, double incl, double part, const VT *v, int K,
-                                 double target, const double *a0, const PT *a1, const int *ai,
-                                 Cand &c) {
-  const bool pos = part > 0.0;
-  const uint64_t bf = ballot(pos);
-  if (bf == 0) return false;
-  const int first = first_set(ballot(pos && incl > target));
-  const int src = first >= 0 ? first : last_set(bf);
-  // every lane searches its own slots as if it owned the pick (no divergent
-  // code); the owner's slot is read afterwards, then its payloads with a
-  // wave-uniform slot index
+// part their sum, incl the team-inclusive prefix of part.  ql is the lane's
+// first slot whose running sum exceeds the target (K if none does); the
+// chosen lane src is the first that has such a slot and a nonzero partial.
+// Every lane searches its own slots as if it owned the pick, so the search
+// does not wait for the choice of the lane; false if no lane has a hit.
+template <int KC, typename VT>
+__device__ __forceinline__ bool wave_search(double incl, double part, const VT *v, int K, double target,
+                                   uint64_t go, int &src, int &ql) {
+  double c[KC];
   double cum = incl - part;
-  int qhit = -1, last = -1;
 #pragma unroll
-  for (int q = 0; q < KMAX; ++q) {
-    if (q < K) {
-      last = v[q] > (VT)0 ? q : last;
-      cum += (double)v[q];
-      qhit = (qhit < 0 && cum > target) ? q : qhit;
-    }
+  for (int q = 0; q < KC; ++q) {
+    if (q < K) cum += (double)v[q];
+    c[q] = cum;
   }
-  const int qs = readlane_i((first >= 0 && qhit >= 0) ? qhit : last, src);
-  c.q = qs;
-  c.lane = wave * 64 + src;
-  c.hit = first >= 0 ? 1 : 0;
-  c.p0 = c.p1 = 0.0;
-  c.gi = -1;
+  ql = KC - 1;
 #pragma unroll
-  for (int q = 0; q < KMAX; ++q) {
-    if (q == qs) {
-      c.p0 = readlane_d(a0[q], src);
-      c.p1 = readlane_d((double)a1[q], src);
-      c.gi = readlane_i(ai[q], src);
-    }
-  }
-  return true;
+  for (int q = KC - 2; q >= 0; --q) ql = c[q] > target ? q : ql;
+  // masks, not conditions, are combined: a ballot of one compare is the
+  // compare itself
+  const uint64_t hit = ballot(part > 0.0) & ballot(c[KC - 1] > target) & go;
+  src = __builtin_ctzll(hit | (1ull << 63));
+  return hit != 0;
 }
 
-// The wave of a multi-wave team that holds the target: the first whose
-// team-inclusive prefix at its last lane exceeds it.  That prefix is rebuilt
-// from the wave totals of the latest exchange with the same FP64 operations
-// the lanes used (offset of the earlier waves, plus the wave's total, plus
-// delta from team lane 64 fix_wave on), so every wave finds the same owner
-// without another exchange.  -1 if no wave's prefix exceeds the target.
-__device__ inline int owner_wave(const Team &tm, double target, int fix_wave, double delta) {
-  double t[4];
-  tm.totals4(0, t);
-  double off = 0.0;
-  int ow = -1;
+// Where rounding leaves no lane of the wave past the target: its last lane
+// with a nonzero partial, and there the last nonzero slot; false if every
+// partial is zero.
+template <int KC, typename VT>
+__device__ __forceinline__ bool wave_last(double part, const VT *v, int K, int &src, int &ql) {
+  const uint64_t pos = ballot(part > 0.0);
+  src = 63 - __builtin_clzll(pos | 1ull);
+  ql = 0;
 #pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    double cum = off + t[w];
-    if (w >= fix_wave) cum += delta;
-    if (ow < 0 && cum > target) ow = w;
-    off += t[w];
-  }
-  return ow;
+  for (int q = 0; q < KC; ++q)
+    if (q < K) ql = v[q] > (VT)0 ? q : ql;
+  return pos != 0;
 }
 
-// Every wave searches and publishes its candidate; the team takes the first
-// wave with a lane past the target, else the last wave with any nonzero
-// partial.  q < 0: nothing to pick.
-template <int KMAX, typename VT, typename PT>
-__device__ inline Cand pick_all_waves(Team &tm, double incl, double part, const VT *v, int K,
-                                      double target, const double *a0, const PT *a1,
-                                      const int *ai) {
-  Cand h{0.0, 0.0, -1, -1, 0, -1};
-  if (!wave_pick<KMAX>(tm.wave, incl, part, v, K, target, a0, a1, ai, h)) h.q = -1;
-  tm.phase ^= 1;
-  if (tm.lane == 0) tm.S->cand[tm.phase][tm.wave] = h;
+// slot ql (per lane) of the lane's values
+template <int KC, typename T>
+__device__ __forceinline__ T lane_pick(const T *a, int ql) {
+  T x = a[0];
+#pragma unroll
+  for (int q = 1; q < KC; ++q) {
+    const T v = a[q];  // a value, not a choice of addresses: the array stays in registers
+    x = ql == q ? v : x;
+  }
+  return x;
+}
+
+// The wave of a four-wave team that holds the target: the first whose prefix
+// p[w] (plus delta from wave fix_wave on) exceeds it.  Every wave has the same
+// prefixes and finds the same owner without another exchange.  -1 if none.
+__device__ __forceinline__ int owner_wave(const double p[4], double target, int fix_wave, double delta) {
+  const uint64_t b0 = ballot((fix_wave <= 0 ? p[0] + delta : p[0]) > target);
+  const uint64_t b1 = ballot((fix_wave <= 1 ? p[1] + delta : p[1]) > target);
+  const uint64_t b2 = ballot((fix_wave <= 2 ? p[2] + delta : p[2]) > target);
+  const uint64_t b3 = ballot((fix_wave <= 3 ? p[3] + delta : p[3]) > target);
+  return b0 ? 0 : (b1 ? 1 : (b2 ? 2 : (b3 ? 3 : -1)));
+}
+
+// A pick as every lane of the team knows it: the chosen slot s (its index in
+// the record store, -1: nothing to pick), the particle's mass m, the chosen
+// value x (row sum of i, relative velocity of j).
+template <typename XT>
+struct Picked {
+  double m;
+  XT x;
+  int s;
+};
+
+// One-wave pick of the chosen slot's values by lane reads.
+template <int KC, typename XT>
+__device__ __forceinline__ Picked<XT> read_pick(int src, int ql, const double *m, const XT *x) {
+  Picked<XT> o;
+  const int qs = readlane_i(ql, src);
+  o.s = qs * 64 + src;
+  o.m = readlane_d(lane_pick<KC>(m, ql), src);
+  o.x = readlane_t(lane_pick<KC>(x, ql), src);
+  return o;
+}
+
+// The chosen lane of a four-wave team publishes its slot: the owner wave's
+// search, or where rounding leaves no lane past the target its last lane with
+// a nonzero partial (slot -1: there is none either) ...
+template <int KC, typename XT>
+__device__ __forceinline__ void write_pick(TeamCand *C, int wave, int lane, int src, int ql, bool any,
+                                           const double *m, const XT *x) {
+  if (lane == src) {
+    C->m = lane_pick<KC>(m, ql);
+    if constexpr (sizeof(XT) == 4)
+      C->xf = lane_pick<KC>(x, ql);
+    else
+      C->x = lane_pick<KC>(x, ql);
+    C->s = any ? ql * 256 + wave * 64 + lane : -1;
+  }
+}
+template <int KC, typename XT, typename VT>
+__device__ __forceinline__ void publish_pick(TeamCand *C, int wave, int lane, double incl,
+                                             double part, const VT *v, int K, double target,
+                                             const double *m, const XT *x) {
+  int src, ql;
+  bool any = true;
+  if (!wave_search<KC>(incl, part, v, K, target, ~0ull, src, ql))
+    any = wave_last<KC>(part, v, K, src, ql);
+  write_pick<KC, XT>(C, wave, lane, src, ql, any, m, x);
+}
+// ... and every lane reads it after the barrier.
+template <typename XT>
+__device__ __forceinline__ Picked<XT> fetch_pick(const TeamCand *C) {
+  Picked<XT> o;
+  o.m = C->m;
+  if constexpr (sizeof(XT) == 4)
+    o.x = C->xf;
+  else
+    o.x = C->x;
+  o.s = __builtin_amdgcn_readfirstlane(C->s);
+  return o;
+}
+
+// Team pick where the owner found no hit (or rounding left no owner): every
+// wave searches; the first wave with a hit wins, else the last wave with any
+// nonzero partial.  s < 0: every partial is zero.
+template <int KC, typename VT, typename XT>
+__device__ __forceinline__ Picked<XT> pick_all_waves(TeamScratch *S, TeamCand *C, int wave, int lane,
+                                            double incl, double part, const VT *v, int K,
+                                            double target, const double *m, const XT *x) {
+  int src, ql;
+  int code = wave_search<KC>(incl, part, v, K, target, ~0ull, src, ql) ? 2 : 0;
+  if (code == 0) code = wave_last<KC>(part, v, K, src, ql) ? 1 : 0;
+  if (lane == 0) S->code[wave] = code;
   block_lds_sync();
   int wsel = -1;
-  for (int w = tm.nw - 1; w >= 0; --w) {
-    const Cand &x = tm.S->cand[tm.phase][w];
-    if (x.q >= 0 && x.hit) wsel = w;
-  }
-  if (wsel < 0) {
-    for (int w = 0; w < tm.nw; ++w)
-      if (tm.S->cand[tm.phase][w].q >= 0) wsel = w;
-  }
-  if (wsel < 0) return Cand{0.0, 0.0, -1, -1, 0, -1};
-  return tm.S->cand[tm.phase][wsel];
-}
-
-// Team-wide selection: one wave searches (the owner of the target) and
-// publishes; if rounding leaves no lane of that wave past the target, every
-// wave searches (pick_all_waves).  The same result on every lane of the team.
-template <int KMAX, typename VT, typename PT>
-__device__ inline Cand team_pick(Team &tm, double incl, double part, const VT *v, int K,
-                                 double target, int fix_wave, double delta, const double *a0,
-                                 const PT *a1, const int *ai) {
-  Cand c{0.0, 0.0, -1, -1, 0, -1};
-  if (tm.nw == 1) {
-    if (!wave_pick<KMAX>(0, incl, part, v, K, target, a0, a1, ai, c)) c.q = -1;
-    return c;
-  }
-  const int ow = owner_wave(tm, target, fix_wave, delta);
-  tm.phase ^= 1;
-  if (tm.wave == ow) {
-    if (!wave_pick<KMAX>(tm.wave, incl, part, v, K, target, a0, a1, ai, c) || !c.hit) c.q = -1;
-    if (tm.lane == 0) tm.S->cand[tm.phase][0] = c;
-  }
+  for (int w = 3; w >= 0; --w)
+    if (S->code[w] == 2) wsel = w;
+  if (wsel < 0)
+    for (int w = 0; w < 4; ++w)
+      if (S->code[w] == 1) wsel = w;
+  if (wave == wsel) write_pick<KC, XT>(C, wave, lane, src, ql, true, m, x);
   block_lds_sync();
-  if (ow >= 0) {
-    c = tm.S->cand[tm.phase][0];
-    if (c.q >= 0) return c;
-  }
-  return pick_all_waves<KMAX>(tm, incl, part, v, K, target, a0, a1, ai);
+  Picked<XT> o = fetch_pick<XT>(C);
+  if (wsel < 0) o.s = -1;
+  block_lds_sync();  // the codes and the candidate are read before they are written again
+  return o;
 }
 
-// Outcome of an event for i (mass mi, swarm mass Mi; the FP32 form takes the
-// record's Mn instead) hitting j's swarm (mass mj) at relative velocity dvj:
-// new mass, outcome code and i's new record.
-// The writer also applies the side effects: the anomaly flag and the
-// mass-weighted composition of i on sticking or fragmentation (lanes below
-// n_comp, one component each).
-// PROB: the probabilistic fragmentation criteria (a kernel variant of its
-// own, so that the sharp criterion carries none of their special functions);
-// u5 is their uniform, from Philox (e, cell, step, 3).  The FP64 form takes
-// the probability in FP64; the mixed form, whose relative velocity is FP32,
-// in FP32
-template <typename RT, bool PROB>
-__device__ inline int event_outcome(const CollideArgs &A, const TeamScratch *S, double mi,
-                                    double mj, double Mi, RT Mn, RT dvj, double u4, double u5,
-                                    int gi, int gj, int lane, bool writer, double &mnew,
-                                    Rec<RT> &rin) {
-  const OutcomeConst &P = S->oc;
-  bool fast;
-  if constexpr (PROB) {
-    fast = u5 < (double)frag_probability(P, dvj);
+// Outcome of an event for i (mass mi) hitting a body of swarm j (mass mj) at
+// relative velocity dv: the new mass, and the counts of the rarer outcomes.
+// fast: the collision fragments or erodes.  The FP64 form takes it from
+// outcome(); the mixed form computes the sticking and the eroding mass side by
+// side with its division-free equivalents (no branch on the common outcomes)
+// and enters a branch only for the fragment draws.  n_fast counts erosions
+// too.  Returns the outcome code where CODE asks for it.
+struct OutcomeCounts {
+  uint32_t n_fast = 0, n_small = 0, n_frag = 0;
+};
+template <typename RT, bool CODE>
+__device__ __forceinline__ int event_outcome(const OutcomeConst &P, bool fast, double mi, double mj,
+                                             double u4, double &mnew, OutcomeCounts &n) {
+  if constexpr (sizeof(RT) == 8) {
+    const int oc = __builtin_amdgcn_readfirstlane(outcome<true>(P, fast, mi, mj, u4, mnew));
+    n.n_fast += oc != OUT_STICK ? 1u : 0u;
+    n.n_small += oc == OUT_ERODED_SMALL ? 1u : 0u;
+    n.n_frag += oc == OUT_FRAG ? 1u : 0u;
+    return oc;
   } else {
-    fast = !(dvj < (RT)P.v_frag);
+    const double d = P.dm_max * mi;
+    const double gm = (P.dm_max > 0.0 && d > mj) ? d : mj;
+    const double er = mi - P.erosion_chi * gm;
+    const double ec = er > P.m0 ? er : P.m0;
+    const double big = mi > mj ? mi : mj, small = mi > mj ? mj : mi;
+    const uint64_t mf = ballot(fast);
+    const uint64_t uneven = ballot(big >= P.erosion_ratio * small);
+    mnew = fast ? ec : mi + gm;
+    int oc = OUT_STICK;
+    if (CODE) oc = mf ? OUT_ERODE : OUT_STICK;
+    n.n_fast += mf ? 1u : 0u;
+    if (mf & ~(uneven & ballot(mi >= mj))) {
+      mnew = frag_draw(P.m0, uneven ? mi : big, u4);
+      n.n_small += uneven ? 1u : 0u;
+      n.n_frag += uneven ? 0u : 1u;
+      if (CODE) oc = uneven ? OUT_ERODED_SMALL : OUT_FRAG;
+    }
+    return oc;
   }
-  const int oc = outcome<sizeof(RT) == 8>(P, fast, mi, mj, u4, mnew);
-  if (writer && (!(mnew > 0.0) || !isfinite(mnew)) && lane == 0)
-    atomicOr(&A.state->flags, FLAG_BAD_MASS);
-  rin = RecAfter<RT>::get(A.P, S, mnew, Mi, Mn);
-  return oc;
 }
 
 // Composition of i after a sticking or fragmenting event: mass-weighted mix
@@ -612,12 +625,424 @@ __device__ inline void log_event(const CollideArgs &A, int cell, uint32_t e, int
 // cell (dt = 0), a time limit dt > 0, or either, read from the arguments
 enum : int { kFixedCount = 0, kTimeLimited = 1, kEitherLimit = 2 };
 
-// AUX: the composition mix and the event log are compiled in (a launch with
-// fractions to track or events to record); without them the event loop
-// carries neither.  LIMIT: a kernel compiled for fixed counts only carries no
-// waiting times (their logarithm, the time test, the priority rule)
-template <typename RT, int KMAX, bool FAST, bool PROB, bool AUX, int NW, int LIMIT = kEitherLimit>
-__device__ void process_cell(const CollideArgs &A, int cell, char *base, int cap, int wave,
+// ---------------------------------------------------------------------------
+// the events of one cell
+// ---------------------------------------------------------------------------
+// KC: slots per lane; with FIXED every lane of the team has exactly KC slots
+// (K == KC), otherwise K <= KC of them.  AUX: the composition mix and the event
+// log are compiled in (a launch with fractions to track or events to record);
+// without them the event loop carries neither.  LIMIT: a kernel compiled for
+// fixed counts only carries no waiting times (their logarithm, the time test,
+// the priority rule).
+//
+// A cell's events are one serial chain, and beyond the 2 K pair evaluations its
+// length is that of an event's control: what the chain waits for counts, not
+// the number of instructions alone.  Hence: the slots per lane are a
+// compile-time number (no branch per slot, one block whose loads and pairs
+// interleave); the tests that end a cell (time limit, vanished total) are part
+// of the selection's ballot, one branch for all of them; a chosen slot's values
+// are selected per lane while the chosen lane is still being found; the
+// outcome's and the new record's parameters are read from LDS while row i is
+// evaluated; the common outcomes are computed without a branch; the rare
+// cases (rounding left no hit, row i without a partner) join the common path
+// instead of leaving the loop body by an exit of their own.
+template <typename RT, int KC, bool FIXED, bool FAST, bool PROB, bool AUX, int NW, int LIMIT>
+__device__ __forceinline__ void run_events(const CollideArgs &A, const PairConst<RT> &pc,
+                                           const RecStore<RT> &R, TeamScratch *S, int cell, int s0,
+                                           int n, int K_cell, double scale, int wave_cell,
+                                           int lane_cell, uint32_t step, double *r, double *m64) {
+  constexpr int TL = 64 * NW;
+  // the records of all slots are requested before the first pair: one wait on
+  // LDS per pass instead of one per slot (a lone cell of 200 particles: 1.84
+  // against 1.94 us per event)
+  constexpr bool AHEAD = FIXED && KC > 1 && sizeof(RT) == 4;
+  const bool timed = LIMIT == kEitherLimit ? A.dt > 0.0 : LIMIT == kTimeLimited;
+  const uint32_t emax = A.max_events > 0 ? (uint32_t)A.max_events : 0xFFFFFFFFu;
+  const uint32_t c32 = (uint32_t)cell;
+  uint32_t e = 0;  // events so far (fewer than 2^32 per cell and step)
+  uint32_t n_null = 0;
+  OutcomeCounts cnt;
+  uint64_t bad_mass = 0;
+  // slots that hold a particle, as lane masks
+  uint64_t valid[KC];
+#pragma unroll
+  for (int q = 0; q < KC; ++q) {
+    const int K = FIXED ? KC : K_cell;
+    valid[q] = ballot(q < K && (wave_cell * 64 + lane_cell) * K + q < n);
+  }
+  // what the previous event leaves to the next scan: the wave-partial new row
+  // sum of its i, i's old row sum and its place (own[q]: its lane, if its slot
+  // is q; own_lane: its team lane).  None before the first event, and none for
+  // a scan repeated on the row sums as they are
+  RT part2 = (RT)0;
+  double ri_old = 0.0;
+  int own_lane = TL;
+  uint64_t own[KC];
+#pragma unroll
+  for (int q = 0; q < KC; ++q) own[q] = 0;
+  double t = 0.0, Rtot = 0.0;
+  // uniforms of 64 consecutive events: lane l holds -ln u1, u2, u3, u4 of
+  // event e0 + l from Philox(e0 + l, cell, step, 0) and (.., 1)
+  double nlu1 = 0.0, uu2 = 0.0, uu3 = 0.0, uu4 = 0.0, uu5 = 0.0;
+  int rl = 0, rl_end = 0;  // the event's lane of that batch, and the batch's end
+  // the previous event's composition mix, not yet stored
+  CompMix pcm{0.0f, 0.0f, false};
+  int p_oc = 0, p_gi = 0;
+  double p_mi = 0.0, p_mj = 0.0;
+  int si = 0;  // the chosen i: slot and mass (its old row sum is ri_old)
+  double mi = 0.0;
+  // what one choice of i passes along: prefix and lane sum of the row sums,
+  // (four-wave teams) the waves' prefixes, their correction and the pick
+  double incl = 0.0, part = 0.0, p[4], delta = 0.0, t_next = 0.0, target = 0.0;
+  uint64_t go = 0;
+  int src = 0, ql = 0;
+  Picked<double> ci;
+
+  // -- prefix of the row sums and the new r_i in one exchange.  The owner's
+  // slot still holds the old r_i and is corrected here; in four-wave teams,
+  // waves from i's on carry delta on top of the prefixes p[]
+  auto scan_rows = [&](int K, int lane, int wave) __attribute__((always_inline)) {
+    const int tl = wave * 64 + lane;
+    part = r[0];  // K >= 1
+#pragma unroll
+    for (int q = 1; q < KC; ++q)
+      if (FIXED || q < K) part += r[q];
+    double ri_new;
+    incl = team_scan<NW, true>(part, part2, wave, lane, S->tot_i, p, Rtot, ri_new);
+    delta = ri_new - ri_old;
+    incl += tl >= own_lane ? delta : 0.0;
+    Rtot += delta;
+    part += tl == own_lane ? delta : 0.0;
+#pragma unroll
+    for (int q = 0; q < KC; ++q)
+      r[q] = __builtin_amdgcn_inverse_ballot_w64(own[q]) ? ri_new : r[q];
+  };
+
+  // the uniforms of the next 64 events, one event per lane
+  auto draw = [&](int lane) __attribute__((always_inline)) {
+    const uint32_t ec = e + (uint32_t)lane;
+    // the key schedule is formed here, once per 64 events, not held
+    const uint32_t k0 = opaque_u(A.P.key0), k1 = opaque_u(A.P.key1);
+    const U4 w0 = philox4x32_10(U4{ec, c32, step, 0u}, k0, k1);
+    const U4 w1 = philox4x32_10(U4{ec, c32, step, 1u}, k0, k1);
+    if (timed) nlu1 = -log(u01(w0.x, w0.y));
+    uu2 = u01(w0.z, w0.w);
+    uu3 = u01(w1.x, w1.y);
+    uu4 = u01(w1.z, w1.w);
+    if constexpr (PROB) {  // the fragmentation uniform u5
+      const U4 w3 = philox4x32_10(U4{ec, c32, step, 3u}, k0, k1);
+      uu5 = u01(w3.x, w3.y);
+    }
+    rl = 0;
+    rl_end = (int)(emax - e < 64u ? emax - e : 64u);
+  };
+
+  // the end of the exponential waiting time; the FP32 form takes 1/R from the
+  // hardware estimate and one Newton step
+  auto next_time = [&](double R) __attribute__((always_inline)) -> double {
+    if (!timed) return t;
+    if constexpr (sizeof(RT) == 4) {
+      double ir = __builtin_amdgcn_rcp(R);
+      ir = fma(fma(-R, ir, 1.0), ir, ir);
+      return t + readlane_d(nlu1, rl) * ir * scale;
+    } else {
+      return t + readlane_d(nlu1, rl) / R * scale;
+    }
+  };
+
+  // -- choose i by cumulative row sums; false: see choose_rare
+  auto choose = [&](int K, int lane, int wave) __attribute__((always_inline)) -> bool {
+    t_next = next_time(Rtot);
+    go = ballot(Rtot > 0.0);
+    if (timed) go &= ballot(!(t_next > A.dt));  // else the next event falls outside the step
+    target = readlane_d(uu2, rl) * Rtot;
+    if constexpr (NW == 1) {
+      return wave_search<KC>(incl, part, r, K, target, go, src, ql);
+    } else {
+      const int ow = go ? owner_wave(p, target, own_lane >> 6, delta) : -1;
+      if (wave == ow)
+        publish_pick<KC, double>(&S->ci, wave, lane, incl, part, r, K, target, m64, r);
+      block_lds_sync();
+      ci = fetch_pick<double>(&S->ci);
+      return (ow | ci.s) >= 0;
+    }
+  };
+  // No hit, the time is over, or the running total vanished.  That total (the
+  // scan plus the change of r_i) can round to zero while a row sum still holds
+  // a positive remainder, and rounding can leave every prefix below the
+  // target: the cell is done only when a fresh sum of the row sums is zero, as
+  // in the method's definition of R.  false: the cell is done
+  auto choose_rare = [&](int K, int lane, int wave) __attribute__((always_inline)) -> bool {
+    const bool fresh = own_lane == TL;
+    bool ok = false;
+    if (NW > 1) block_lds_sync();
+    if (ballot(Rtot > 0.0)) {
+      if (ballot(isfinite(Rtot)) == 0 || go == 0) return false;
+      if constexpr (NW == 1) {
+        ok = wave_last<KC>(part, r, K, src, ql);
+      } else {
+        ci = pick_all_waves<KC, double, double>(S, &S->ci, wave, lane, incl, part, r, K,
+                                                     target, m64, r);
+        ok = ci.s >= 0;
+      }
+    }
+    if (ok) return true;
+    // a total of rounding remainders ends the cell; a positive fresh total
+    // takes the event on the fresh prefixes
+    if (!fresh) {
+      part = r[0];
+#pragma unroll
+      for (int q = 1; q < KC; ++q)
+        if (FIXED || q < K) part += r[q];
+      double unused;
+      incl = team_scan<NW, false>(part, 0.0f, wave, lane, S->tot_i, p, Rtot, unused);
+      t_next = next_time(Rtot);
+      if (ballot(Rtot > 0.0) == 0 || ballot(isfinite(Rtot)) == 0) return false;
+      if (timed && ballot(t_next > A.dt)) return false;
+      target = readlane_d(uu2, rl) * Rtot;
+      if constexpr (NW == 1) {
+        ok = wave_search<KC>(incl, part, r, K, target, ~0ull, src, ql) ||
+             wave_last<KC>(part, r, K, src, ql);
+      } else {
+        block_lds_sync();
+        ci = pick_all_waves<KC, double, double>(S, &S->ci, wave, lane, incl, part, r, K,
+                                                     target, m64, r);
+        ok = ci.s >= 0;
+      }
+    } else if (ballot(Rtot > 0.0) == 0) {
+      return false;
+    }
+    if (!ok && wave * 64 + lane == 0) atomicOr(&A.state->flags, FLAG_BAD_RATE);
+    return ok;
+  };
+  auto take = [&]() __attribute__((always_inline)) {
+    if constexpr (NW == 1) ci = read_pick<KC, double>(src, ql, m64, r);
+    t = t_next;
+    si = ci.s;
+    mi = ci.m;
+    ri_old = ci.x;
+  };
+
+  bool any;
+  {
+    const int wave = NW == 1 ? 0 : wave_cell;
+    scan_rows(K_cell, lane_cell, wave);
+    if (timed) {
+      // time-limited steps: a cell whose expected event count R dt is large is
+      // a long serial chain that can outlast every other cell of the step, so
+      // its waves get a higher issue priority on their SIMD (the rest fill in
+      // around them); back to the default when the cell is done
+      const double expect = Rtot / scale * A.dt;
+      if (expect >= 256.0)
+        __builtin_amdgcn_s_setprio(3);
+      else if (expect >= 64.0)
+        __builtin_amdgcn_s_setprio(2);
+      else if (expect >= 16.0)
+        __builtin_amdgcn_s_setprio(1);
+    }
+    draw(lane_cell);
+    any = choose(K_cell, lane_cell, wave) || choose_rare(K_cell, lane_cell, wave);
+  }
+  // The scan and the choice of the next event's i stand at the end of the loop
+  // body, after the update of the row sums, so that they are scheduled
+  // together; the rare ways out leave the loop directly.
+  if (any) for (;;) {
+    take();
+    // lane and wave indices (and K) per event: lane masks formed from them are
+    // made where they are needed instead of being kept across the loop
+    const int K = FIXED ? KC : opaque_s(K_cell);
+    const int lane = opaque_v(lane_cell);
+    const int wave = NW == 1 ? 0 : opaque_s(wave_cell);
+    const int tl = wave * 64 + lane;
+    if constexpr (AUX) {
+      if (pcm.on) {
+        comp_store<sizeof(RT) == 8>(A, pcm, lane, p_oc, p_gi, p_mi, p_mj);
+        pcm.on = false;
+      }
+    }
+    // particle indices are read from the cell order where an event needs them
+    // (fractions; the FP64 state of i, rebuilt from its swarm mass): the loads
+    // overlap the rows, and no register holds them through the events
+    int gi = 0;
+    double Mi = 0.0;
+    if constexpr (AUX || sizeof(RT) == 8) gi = A.order[s0 + (si & (TL - 1)) * K + si / TL];
+    if constexpr (sizeof(RT) == 8) Mi = A.M[gi];
+    const Rec<RT> ri = R.load(si);
+
+    Rec<RT> rq[KC];
+    if constexpr (AHEAD) {
+#pragma unroll
+      for (int q = 0; q < KC; ++q) rq[q] = R.load(q * TL + tl);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // -- row i before the event: r_ij, r_ji and the relative velocities
+    RT rij[KC], rji[KC], dvv[KC];
+    double part1 = 0.0;
+#pragma unroll
+    for (int q = 0; q < KC; ++q) {
+      rij[q] = (RT)0;
+      rji[q] = (RT)0;
+      dvv[q] = (RT)0;
+      if (FIXED || q < K) {  // empty slots have zero density: rij = 0
+        if constexpr (!AHEAD) rq[q] = R.load(q * TL + tl);
+        PairEval<RT, FAST>::run(pc, ri, rq[q], dvv[q], rij[q], rji[q]);
+      }
+      part1 = q == 0 ? (double)rij[0] : part1 + (double)rij[q];
+    }
+    // the outcome's and the new record's parameters, read while the scan runs
+    OutcomeConst oc_par;
+    CellF cf;
+    if constexpr (sizeof(RT) == 4) {
+      oc_par = S->oc;
+      cf = S->cf;
+    }
+    double Ri, pj[4];
+    double unused;
+    const double incl1 =
+        team_scan<NW, false>(part1, 0.0f, wave, lane, S->tot_j, pj, Ri, unused);
+    if constexpr (sizeof(RT) == 4) {
+      asm volatile("" ::"v"(oc_par.dm_max), "v"(oc_par.erosion_chi), "v"(oc_par.erosion_ratio),
+                   "v"(oc_par.m0), "v"(oc_par.v_frag));
+      asm volatile("" ::"v"(cf.ca), "v"(cf.a_sw), "v"(cf.tE), "v"(cf.tS), "v"(cf.Om), "v"(cf.Ste),
+                   "v"(cf.m2eta), "v"(cf.meta), "v"(cf.mzO));
+    } else {
+      oc_par = S->oc;
+    }
+    // row i may have no partner left (its stored sum was rounding residue):
+    // a null event clears it.  It takes the common path with every update
+    // masked out
+    const bool null = ballot(Ri > 0.0) == 0;
+    // -- choose j (its mass, relative velocity, index), then the outcome
+    // (only i changes), computed alike by every wave
+    const double target_j = readlane_d(uu3, rl) * Ri;
+    Picked<RT> cj;
+    if constexpr (NW == 1) {
+      if (!wave_search<KC>(incl1, part1, rij, K, target_j, ~0ull, src, ql))
+        wave_last<KC>(part1, rij, K, src, ql);
+      cj = read_pick<KC, RT>(src, ql, m64, dvv);
+    } else {
+      const int ow = owner_wave(pj, target_j, NW, 0.0);
+      if (wave == ow)
+        publish_pick<KC, RT>(&S->cj, wave, lane, incl1, part1, rij, K, target_j, m64, dvv);
+      block_lds_sync();
+      cj = fetch_pick<RT>(&S->cj);
+      if ((ow < 0 || cj.s < 0) && !null) {
+        block_lds_sync();
+        cj = pick_all_waves<KC, RT, RT>(S, &S->cj, wave, lane, incl1, part1, rij, K, target_j,
+                                             m64, dvv);
+      }
+    }
+    CompMix cm{0.0f, 0.0f, false};
+    if constexpr (AUX)
+      if (!null && A.comp != nullptr && wave == 0)
+        cm = comp_load(A, lane, true, gi, A.order[s0 + (cj.s & (TL - 1)) * K + cj.s / TL]);
+    bool fast;
+    if constexpr (PROB) {
+      fast = readlane_d(uu5, rl) < (double)frag_probability(oc_par, cj.x);
+    } else {
+      fast = !(cj.x < (RT)oc_par.v_frag);
+    }
+    if (null) {
+      cj.m = 0.0;
+      fast = false;
+      ++n_null;
+    }
+    double mnew;
+    const int oc = event_outcome<RT, AUX>(oc_par, fast, mi, cj.m, readlane_d(uu4, rl), mnew, cnt);
+    bad_mass |= ballot(!(mnew > 0.0) || !isfinite(mnew));
+    const Rec<RT> rin = RecAfter<RT>::get(A.P, S, cf, mnew, Mi, ri.Mn);
+    if constexpr (AUX) {
+      if (A.evlog != nullptr && tl == 0)
+        log_event(A, cell, e, (si & (TL - 1)) * K + si / TL,
+                  null ? -1 : (cj.s & (TL - 1)) * K + cj.s / TL, null ? -1 : oc);
+    }
+    // the owner of i keeps the new record and mass; it alone reads the slot
+    // until the next exchange.  own[q]: its lane, if the slot is q
+    const int qi = si / TL;
+    own_lane = si & (TL - 1);
+    const uint64_t own_bit = NW == 1 || wave == own_lane >> 6 ? 1ull << (si & 63) : 0ull;
+#pragma unroll
+    for (int q = 0; q < KC; ++q) own[q] = (KC == 1 || q == qi) ? own_bit : 0ull;
+    if (__builtin_amdgcn_inverse_ballot_w64(null ? 0ull : own_bit)) R.store(si, rin);
+
+    // -- new row i: incremental update of the other rows, fresh row sum of
+    // i in the rate precision within a wave (the FP32 tree adds no more
+    // than the rates' own rounding), then FP64
+    part2 = (RT)0;
+    if constexpr (AHEAD) {
+#pragma unroll
+      for (int q = 0; q < KC; ++q) rq[q] = R.load(q * TL + tl);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int q = 0; q < KC; ++q) {
+      if (FIXED || q < K) {
+        if constexpr (!AHEAD) rq[q] = R.load(q * TL + tl);
+        RT dv, a_iq, a_qi;
+        PairEval<RT, FAST>::run(pc, rin, rq[q], dv, a_iq, a_qi);
+        part2 = q == 0 ? a_iq : part2 + a_iq;
+        // FP64: old term out, new term in, as the oracle orders them; FP32:
+        // the change of r_qi in FP32 (one rounding of a difference far
+        // below the row sum), then one FP64 addition.  Empty slots stay 0,
+        // and the owner's slot keeps the old r_i until the new one is summed
+        const uint64_t upd = null ? 0ull : valid[q] & ~own[q];
+        const bool v = __builtin_amdgcn_inverse_ballot_w64(upd);
+        if constexpr (sizeof(RT) == 8) {
+          const double x = (r[q] - (double)rji[q]) + (double)a_qi;
+          r[q] = v ? __builtin_fmax(x, 0.0) : r[q];
+        } else {
+          const float d = opaque_v(v ? a_qi - rji[q] : 0.0f);
+          r[q] = __builtin_fmax(r[q] + (double)d, 0.0);
+        }
+        m64[q] = !null && __builtin_amdgcn_inverse_ballot_w64(own[q]) ? mnew : m64[q];
+      }
+    }
+    if constexpr (AUX) {
+      pcm = cm;
+      p_oc = oc;
+      p_gi = gi;
+      p_mi = mi;
+      p_mj = cj.m;
+    }
+    if (null) part2 = (RT)0;
+    scan_rows(K, lane, wave);
+    ++e;
+    if (__builtin_expect(++rl == rl_end, 0)) {
+      if (e >= emax) break;
+      draw(lane);
+    }
+    if (__builtin_expect(!choose(K, lane, wave), 0))
+      if (!choose_rare(K, lane, wave)) break;
+  }
+  if constexpr (AUX) {
+    if (pcm.on) comp_store<sizeof(RT) == 8>(A, pcm, lane_cell, p_oc, p_gi, p_mi, p_mj);
+  }
+  // masses back to HBM (their places are read again rather than held)
+  const int tl = wave_cell * 64 + lane_cell;
+#pragma unroll
+  for (int q = 0; q < KC; ++q) {
+    const int K = FIXED ? KC : K_cell, j = tl * K + q;
+    if ((FIXED || q < K) && j < n) A.m[A.order[s0 + j]] = m64[q];
+  }
+  const bool bad_rate = !isfinite(Rtot);
+  if (tl == 0) {
+    if (bad_rate) atomicOr(&A.state->flags, FLAG_BAD_RATE);
+    if (bad_mass) atomicOr(&A.state->flags, FLAG_BAD_MASS);
+    const uint32_t n_erode = cnt.n_fast - cnt.n_small - cnt.n_frag;
+    const uint32_t n_stick = e - n_null - cnt.n_fast;
+    atomicAdd(&A.state->events, (unsigned long long)e);
+    if (n_stick) atomicAdd(&A.state->outcomes[OUT_STICK], (unsigned long long)n_stick);
+    if (n_erode) atomicAdd(&A.state->outcomes[OUT_ERODE], (unsigned long long)n_erode);
+    if (cnt.n_small)
+      atomicAdd(&A.state->outcomes[OUT_ERODED_SMALL], (unsigned long long)cnt.n_small);
+    if (cnt.n_frag) atomicAdd(&A.state->outcomes[OUT_FRAG], (unsigned long long)cnt.n_frag);
+  }
+  __builtin_amdgcn_s_setprio(0);
+}
+
+template <typename RT, int KMAX, bool FAST, bool PROB, bool AUX, int NW, int LIMIT = kEitherLimit,
+          bool BY_K = false>
+__device__ __forceinline__ void process_cell(const CollideArgs &A, int cell, char *base, int cap, int wave,
                              int lane, uint32_t step) {
   constexpr int nw = NW;  // waves of the team: 1, or 4 (a compile-time shape per cell body)
   const int s0 = __builtin_amdgcn_readfirstlane(A.cell_start[cell]);
@@ -626,14 +1051,8 @@ __device__ void process_cell(const CollideArgs &A, int cell, char *base, int cap
   const int TL = 64 * nw;
   const int K = (n + TL - 1) / TL;
   const RecStore<RT> R(base, cap);
-  Team tm;
-  tm.nw = nw;
-  tm.wave = wave;
-  tm.lane = lane;
-  tm.tl = wave * 64 + lane;
-  tm.S = (TeamScratch *)(base + (size_t)cap * rec_bytes<RT>());
-  tm.phase = 0;
-  const int tl = tm.tl;
+  TeamScratch *const S = (TeamScratch *)(base + (size_t)cap * rec_bytes<RT>());
+  const int tl = wave * 64 + lane;
   if (K > KMAX || K * TL > cap) {
     if (tl == 0) atomicOr(&A.state->flags, FLAG_CAPACITY);
     return;
@@ -672,9 +1091,9 @@ __device__ void process_cell(const CollideArgs &A, int cell, char *base, int cap
   if (sizeof(RT) == 4) {
     ndmax = wave_max_nonneg(ndmax);
     if (nw > 1) {
-      if (lane == 0) tm.S->tot[0][wave] = ndmax;
+      if (lane == 0) S->tot_i[wave] = ndmax;
       block_lds_sync();
-      for (int w = 0; w < nw; ++w) ndmax = fmax(ndmax, tm.S->tot[0][w]);
+      for (int w = 0; w < nw; ++w) ndmax = fmax(ndmax, S->tot_i[w]);
       block_lds_sync();
     }
     int e2 = 0;
@@ -682,20 +1101,18 @@ __device__ void process_cell(const CollideArgs &A, int cell, char *base, int cap
     scale = ldexp(1.0, -e2);
   }
   if (tl == 0) {
-    tm.S->gas = g;
-    tm.S->cf = make_cellf(A.P, g, scale);
-    tm.S->oc = make_outcome_const(A.P);
+    S->gas = g;
+    S->cf = make_cellf(A.P, g, scale);
+    S->oc = make_outcome_const(A.P);
   }
-  uint32_t valid = 0;  // bit q: slot q holds a particle
 #pragma unroll
   for (int q = 0; q < KMAX; ++q) {
     if (q < K) {
       const bool v = tl * K + q < n;
-      valid |= v ? (1u << q) : 0u;
       R.store(q * TL + tl, v ? make_rec<RT>(A.P, g, m64[q], A.M[gix[q]], scale) : empty_rec<RT>());
     }
   }
-  tm.sync();
+  team_sync<NW>();
 
   // ---- row sums r_i = sum_k r_ik ------------------------------------------
   // The FP32 form evaluates each unordered pair once (build_rows_pairwise,
@@ -754,272 +1171,35 @@ __device__ void process_cell(const CollideArgs &A, int cell, char *base, int cap
 #pragma unroll
     for (int q = 0; q < KMAX; ++q)
       if (q < K && tl * K + q < n) A.rowsum_dump[s0 + tl * K + q] = r[q] / scale;
-    tm.sync();
+    team_sync<NW>();
     return;
   }
 
   // ---- events ------------------------------------------------------------
-  double t = 0.0;
-  uint32_t e = 0;  // events so far (fewer than 2^32 per cell and step)
-  uint32_t oc_count[4] = {0u, 0u, 0u, 0u};
-  const uint32_t c32 = (uint32_t)cell;
-  const bool timed = LIMIT == kEitherLimit ? A.dt > 0.0 : LIMIT == kTimeLimited;
-  const uint32_t emax = A.max_events > 0 ? (uint32_t)A.max_events : 0xFFFFFFFFu;
-  double part = 0.0, Rtot;
-#pragma unroll
-  for (int q = 0; q < KMAX; ++q)
-    if (q < K) part += r[q];
-  double incl = tm.scan(part, Rtot);
-  // time-limited steps: a cell whose expected event count R dt is large is a
-  // long serial chain that can outlast every other cell of the step, so its
-  // waves get a higher issue priority on their SIMD (the rest fill in around
-  // them); back to the default when the cell is done
-  if (timed) {
-    const double expect = Rtot / scale * A.dt;
-    if (expect >= 256.0)
-      __builtin_amdgcn_s_setprio(3);
-    else if (expect >= 64.0)
-      __builtin_amdgcn_s_setprio(2);
-    else if (expect >= 16.0)
-      __builtin_amdgcn_s_setprio(1);
-  }
-  // lanes from team lane 64 fix_wave on carry delta on top of the latest
-  // scanned prefix (the new row sum of the previous event's i)
-  int fix_wave = nw;
-  double delta = 0.0;
-  // uniforms of 64 consecutive events: lane l holds -ln u1, u2, u3, u4 of
-  // event e0 + l from Philox(e0 + l, cell, step, 0) and (.., 1)
-  double nlu1 = 0.0, uu2 = 0.0, uu3 = 0.0, uu4 = 0.0, uu5 = 0.0;
-  uint32_t e0 = 0u - 64u;  // first event of the current batch (none yet)
-  // the previous event's composition mix, not yet stored
-  CompMix pcm{0.0f, 0.0f, false};
-  int p_oc = 0, p_gi = 0;
-  double p_mi = 0.0, p_mj = 0.0;
-  const int K_cell = K, lane_cell = lane, wave_cell = wave;
-  for (;;) {
-    // K and the lane / wave indices per event: tests such as q < K, w < wave
-    // or lane == 63 are made where they are needed instead of being kept as
-    // lane masks across the loop
-    const int K = opaque_s(K_cell);
-    tm.lane = opaque_v(lane_cell);
-    tm.wave = opaque_s(wave_cell);
-    if (!(Rtot > 0.0) || !isfinite(Rtot)) {
-      if (!isfinite(Rtot)) {
-        if (tl == 0) atomicOr(&A.state->flags, FLAG_BAD_RATE);
+  if constexpr (BY_K) {
+    static_assert(KMAX == 4, "one event loop per number of slots");
+    switch (K) {
+      case 1:
+        run_events<RT, 1, true, FAST, PROB, AUX, NW, LIMIT>(A, pc, R, S, cell, s0, n, K, scale, wave,
+                                                            lane, step, r, m64);
         break;
-      }
-      // the running total (the last scan plus the change of r_i) can round
-      // to zero while a row sum still holds a positive remainder: the cell
-      // is done only when a fresh sum of the row sums is zero, as in the
-      // method's definition of R
-      if (fix_wave == nw) break;
-      part = 0.0;
-#pragma unroll
-      for (int q = 0; q < KMAX; ++q)
-        if (q < K) part += r[q];
-      incl = tm.scan(part, Rtot);
-      fix_wave = nw;
-      delta = 0.0;
-      if (!(Rtot > 0.0)) break;
+      case 2:
+        run_events<RT, 2, true, FAST, PROB, AUX, NW, LIMIT>(A, pc, R, S, cell, s0, n, K, scale, wave,
+                                                            lane, step, r, m64);
+        break;
+      case 3:
+        run_events<RT, 3, true, FAST, PROB, AUX, NW, LIMIT>(A, pc, R, S, cell, s0, n, K, scale, wave,
+                                                            lane, step, r, m64);
+        break;
+      default:
+        run_events<RT, 4, true, FAST, PROB, AUX, NW, LIMIT>(A, pc, R, S, cell, s0, n, K, scale, wave,
+                                                            lane, step, r, m64);
     }
-    if (e >= emax) break;
-    if (e - e0 >= 64) {
-      e0 = e;
-      const uint32_t ec = (uint32_t)(e + lane);
-      // the key schedule is formed here, once per 64 events, not held
-      const uint32_t k0 = opaque_u(A.P.key0), k1 = opaque_u(A.P.key1);
-      const U4 w0 = philox4x32_10(U4{ec, c32, step, 0u}, k0, k1);
-      const U4 w1 = philox4x32_10(U4{ec, c32, step, 1u}, k0, k1);
-      if (timed) nlu1 = -log(u01(w0.x, w0.y));
-      uu2 = u01(w0.z, w0.w);
-      uu3 = u01(w1.x, w1.y);
-      uu4 = u01(w1.z, w1.w);
-      if constexpr (PROB) {  // the fragmentation uniform u5
-        const U4 w3 = philox4x32_10(U4{ec, c32, step, 3u}, k0, k1);
-        uu5 = u01(w3.x, w3.y);
-      }
-    }
-    const int rl = (int)(e - e0);
-    double t_next = t;
-    if (timed) {
-      // exponential waiting time; the FP32 form takes 1/R from the hardware
-      // estimate and one Newton step
-      double tau;
-      if constexpr (sizeof(RT) == 4) {
-        double ir = __builtin_amdgcn_rcp(Rtot);
-        ir = fma(fma(-Rtot, ir, 1.0), ir, ir);
-        tau = readlane_d(nlu1, rl) * ir * scale;
-      } else {
-        tau = readlane_d(nlu1, rl) / Rtot * scale;
-      }
-      if (t + tau > A.dt) break;  // the next event falls outside the step
-      t_next = t + tau;
-    }
-
-    // -- choose i by cumulative row sums (payloads: m_i, old r_i, index)
-    const Cand ci = team_pick<KMAX>(tm, incl, part, r, K, readlane_d(uu2, rl) * Rtot, fix_wave,
-                                    delta, m64, r, gix);
-    if (ci.q < 0) {
-      // no row sum is positive in the running prefixes: decide on a fresh
-      // sum (a total of rounding remainders ends the cell; a positive fresh
-      // total retries the event on the fresh prefixes)
-      if (fix_wave != nw) {
-        part = 0.0;
-#pragma unroll
-        for (int q = 0; q < KMAX; ++q)
-          if (q < K) part += r[q];
-        incl = tm.scan(part, Rtot);
-        fix_wave = nw;
-        delta = 0.0;
-        if (!(Rtot > 0.0)) break;
-        continue;
-      }
-      if (tl == 0) atomicOr(&A.state->flags, FLAG_BAD_RATE);
-      break;
-    }
-    if constexpr (AUX) {
-      if (pcm.on) {
-        comp_store<sizeof(RT) == 8>(A, pcm, lane, p_oc, p_gi, p_mi, p_mj);
-        pcm.on = false;
-      }
-    }
-    t = t_next;
-    const int si = ci.q * TL + ci.lane;
-    const int i_local = ci.lane * K + ci.q;
-    const double mi = ci.p0, ri_old = ci.p1;
-    const int gi = ci.gi;
-    // the FP64 state of i is rebuilt from its swarm mass (the load overlaps
-    // row i); the FP32 record carries it
-    const double Mi = sizeof(RT) == 8 ? A.M[gi] : 0.0;
-    const Rec<RT> ri = R.load(si);
-
-    // -- row i before the event: r_ij, r_ji and the relative velocities
-    RT rij[KMAX], rji[KMAX], dvv[KMAX];
-    double part1 = 0.0;
-#pragma unroll
-    for (int q = 0; q < KMAX; ++q) {
-      rij[q] = (RT)0;
-      rji[q] = (RT)0;
-      dvv[q] = (RT)0;
-      if (q < K) {  // empty slots have zero density: rij = 0
-        const Rec<RT> rq = R.load(q * TL + tl);
-        PairEval<RT, FAST>::run(pc, ri, rq, dvv[q], rij[q], rji[q]);
-      }
-      part1 += (double)rij[q];
-    }
-    double Ri;
-    const double incl1 = tm.scan(part1, Ri);
-    if (!(Ri > 0.0)) {
-      // row i has no partner left (its stored sum was rounding residue):
-      // clear it and count a null event
-      if (tl == ci.lane) {
-#pragma unroll
-        for (int q = 0; q < KMAX; ++q)
-          if (q == ci.q) r[q] = 0.0;
-      }
-      if constexpr (AUX) {
-        if (tl == 0) log_event(A, cell, e, i_local, -1, -1);
-      }
-      ++e;
-      part = 0.0;
-#pragma unroll
-      for (int q = 0; q < KMAX; ++q)
-        if (q < K) part += r[q];
-      incl = tm.scan(part, Rtot);
-      fix_wave = nw;
-      delta = 0.0;
-      continue;
-    }
-
-    // -- choose j (payloads: m_j, relative velocity, index), then the outcome
-    // (only i changes), computed alike by every wave; wave 0 writes
-    const Cand cj = team_pick<KMAX>(tm, incl1, part1, rij, K, readlane_d(uu3, rl) * Ri, nw, 0.0,
-                                    m64, dvv, gix);
-    CompMix cm{0.0f, 0.0f, false};
-    if constexpr (AUX) cm = comp_load(A, lane, wave == 0, gi, cj.gi);
-    double mnew = 0.0;
-    Rec<RT> rin;
-    const int oc = event_outcome<RT, PROB>(A, tm.S, mi, cj.p0, Mi, ri.Mn, (RT)cj.p1,
-                                           readlane_d(uu4, rl),
-                                           PROB ? readlane_d(uu5, rl) : 0.0, gi, cj.gi, lane,
-                                           wave == 0, mnew, rin);
-    if constexpr (AUX) {
-      if (tl == 0) log_event(A, cell, e, i_local, cj.lane * K + cj.q, oc);
-    }
-    // the owner of i keeps the new mass and record; it alone reads the slot
-    // until the next exchange
-    if (tl == ci.lane) {
-#pragma unroll
-      for (int q = 0; q < KMAX; ++q)
-        if (q == ci.q) m64[q] = mnew;
-      R.store(si, rin);
-    }
-
-    // -- new row i: incremental update of the other rows, fresh row sum of i
-    // the fresh row sum of i: in the rate precision within a wave (the FP32
-    // tree adds no more than the rates' own rounding), then FP64
-    RT part2 = (RT)0;
-#pragma unroll
-    for (int q = 0; q < KMAX; ++q) {
-      if (q < K) {
-        const int s = q * TL + tl;
-        const Rec<RT> rq = R.load(s);
-        RT dv, a_iq, a_qi;
-        PairEval<RT, FAST>::run(pc, rin, rq, dv, a_iq, a_qi);
-        part2 += a_iq;
-        // FP64: old term out, new term in, as the oracle orders them; FP32:
-        // the change of r_qi in FP32 (one rounding of a difference far
-        // below the row sum), then one FP64 addition
-        const double x = sizeof(RT) == 8 ? (r[q] - (double)rji[q]) + (double)a_qi
-                                         : r[q] + (double)(a_qi - rji[q]);
-        const bool upd = s != si && ((valid >> q) & 1u);
-        r[q] = upd ? (x > 0.0 ? x : 0.0) : r[q];
-      }
-    }
-    // next event's prefix of the row sums and the new r_i in one exchange;
-    // the owner's slot still holds the old r_i and is corrected afterwards
-    part = 0.0;
-#pragma unroll
-    for (int q = 0; q < KMAX; ++q)
-      if (q < K) part += r[q];
-    double ri_new;
-    incl = tm.scan2(part, part2, Rtot, ri_new);
-    delta = ri_new - ri_old;
-    fix_wave = ci.lane >> 6;
-    if (tl >= ci.lane) incl += delta;
-    Rtot += delta;
-    if (tl == ci.lane) {
-      part += delta;
-#pragma unroll
-      for (int q = 0; q < KMAX; ++q)
-        if (q == ci.q) r[q] = ri_new;
-    }
-    if constexpr (AUX) {
-      pcm = cm;
-      p_oc = oc;
-      p_gi = gi;
-      p_mi = mi;
-      p_mj = cj.p0;
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) oc_count[k] += (oc == k) ? 1u : 0u;
-    ++e;
+  } else {
+    run_events<RT, KMAX, false, FAST, PROB, AUX, NW, LIMIT>(A, pc, R, S, cell, s0, n, K, scale, wave,
+                                                            lane, step, r, m64);
   }
-  if constexpr (AUX) {
-    if (pcm.on) comp_store<sizeof(RT) == 8>(A, pcm, lane, p_oc, p_gi, p_mi, p_mj);
-  }
-  // masses back to HBM
-#pragma unroll
-  for (int q = 0; q < KMAX; ++q)
-    if (q < K && tl * K + q < n) A.m[gix[q]] = m64[q];
-  if (tl == 0) {
-    atomicAdd(&A.state->events, (unsigned long long)e);
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      if (oc_count[k]) atomicAdd(&A.state->outcomes[k], (unsigned long long)oc_count[k]);
-  }
-  __builtin_amdgcn_s_setprio(0);
-  tm.sync();  // the region is reused by the next cell
+  team_sync<NW>();  // the region is reused by the next cell
 }
 
 // ---------------------------------------------------------------------------
@@ -1027,8 +1207,22 @@ __device__ void process_cell(const CollideArgs &A, int cell, char *base, int cap
 // on four-wave teams (largest first), then small cells on single waves
 // (largest first), each wave popping its own work
 // ---------------------------------------------------------------------------
+//
+// Waves per SIMD the mixed form's registers are limited to: three for fixed
+// counts (every cell a long chain: throughput) and with the composition mix;
+// two for time-limited steps without it, where a few cells' chains or the
+// row-sum builds set the pace and spills cost more than the third wave gives
+// (first steps of a 5e5 disk: 1.76 against 1.85 ms for four; one column: 2.71
+// against 2.77 ms per step; with 8 fractions, 2e6 particles: 5.45 against
+// 5.15 ms, so not there)
+template <typename RT, bool AUX, int LIMIT>
+constexpr int waves_per_simd() {
+  return sizeof(RT) == 4 && (AUX || LIMIT == kFixedCount) ? 3 : 2;
+}
+
 template <typename RT, int KMAX, bool FAST, bool PROB, bool AUX, int LIMIT = kEitherLimit>
-__global__ __launch_bounds__(256, sizeof(RT) == 4 ? 3 : 2) void collide_batched(CollideArgs A) {
+__global__ __launch_bounds__(256, (waves_per_simd<RT, AUX, LIMIT>())) void collide_batched(
+    CollideArgs A) {
   extern __shared__ __align__(16) char smem[];
   __shared__ int s_item;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -1058,10 +1252,11 @@ __global__ __launch_bounds__(256, sizeof(RT) == 4 ? 3 : 2) void collide_batched(
       cell = __builtin_amdgcn_readfirstlane(A.small_list[item]);
     }
     if (nw == 4)
-      process_cell<RT, KMAX, FAST, PROB, AUX, 4, LIMIT>(A, cell, smem, A.big_cap, wave, lane, step);
+      process_cell<RT, KMAX, FAST, PROB, AUX, 4, LIMIT, KMAX == 4>(A, cell, smem, A.big_cap, wave,
+                                                                   lane, step);
     else
-      process_cell<RT, KMAX, FAST, PROB, AUX, 1, LIMIT>(A, cell, smem + (size_t)wave * small_bytes,
-                                                  A.small_cap, 0, lane, step);
+      process_cell<RT, KMAX, FAST, PROB, AUX, 1, LIMIT, KMAX == 4>(
+          A, cell, smem + (size_t)wave * small_bytes, A.small_cap, 0, lane, step);
   }
 }
 

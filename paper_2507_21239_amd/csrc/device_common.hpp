@@ -112,6 +112,15 @@ __device__ inline float dpp_f(float x) {
       __builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, ROW_MASK, BANK_MASK, true));
 }
 
+template <int CTRL, int ROW_MASK, int BANK_MASK>
+__device__ inline float dpp_t(float x) {
+  return dpp_f<CTRL, ROW_MASK, BANK_MASK>(x);
+}
+template <int CTRL, int ROW_MASK, int BANK_MASK>
+__device__ inline double dpp_t(double x) {
+  return dpp_d<CTRL, ROW_MASK, BANK_MASK>(x);
+}
+
 // inclusive prefix sum over the 64 lanes: shifts of 1, 2, 4, 8 inside rows of
 // 16 lanes, then row broadcasts of lanes 15 and 31 (gfx9 DPP)
 __device__ inline float wave_incl_scan(float x) {
@@ -131,6 +140,28 @@ __device__ inline double wave_incl_scan(double x) {
   x += dpp_d<0x142, 0xa, 0xf>(x);  // row_bcast:15 into rows 1, 3
   x += dpp_d<0x143, 0xc, 0xf>(x);  // row_bcast:31 into rows 2, 3
   return x;
+}
+
+// two prefix sums at once (FP64 and the rate precision), step by step, so that
+// the lanes' moves of one fill the wait states of the other
+template <typename T>
+__device__ __forceinline__ void wave_incl_scan2(double &x, T &y) {
+  auto step = [&](auto sx, auto sy) __attribute__((always_inline)) {
+    const double dx = sx(x);
+    const T dy = sy(y);
+    x += dx;
+    y += dy;
+  };
+#define MCD_SCAN_STEP(CTRL, ROWS)                                                       \
+  step([](double v) __attribute__((always_inline)) { return dpp_d<CTRL, ROWS, 0xf>(v); }, \
+       [](T v) __attribute__((always_inline)) { return dpp_t<CTRL, ROWS, 0xf>(v); })
+  MCD_SCAN_STEP(0x111, 0xf);
+  MCD_SCAN_STEP(0x112, 0xf);
+  MCD_SCAN_STEP(0x114, 0xf);
+  MCD_SCAN_STEP(0x118, 0xf);
+  MCD_SCAN_STEP(0x142, 0xa);
+  MCD_SCAN_STEP(0x143, 0xc);
+#undef MCD_SCAN_STEP
 }
 
 // maximum over the 64 lanes (non-negative inputs), returned on every lane

@@ -70,21 +70,29 @@ struct CollideArgs {
   double *rowsum_dump;  // test path: starting row sums written here, no events
 };
 
-// a selection result: payloads of the chosen slot, its slot and team lane
-struct Cand {
-  double p0, p1;
-  int q, lane, hit, gi;
+// a published selection of a four-wave team: mass of the chosen particle, the
+// chosen value (FP64 row sum, or relative velocity in the rate precision) and
+// slot
+struct alignas(16) TeamCand {
+  double m;
+  union {
+    double x;
+    float xf;
+  };
+  int s, pad[3];
 };
 
-// team scratch after a region's particle records: wave totals, selection
-// candidates (double-buffered), the cell's gas state and the outcome
+// team scratch after a region's particle records: wave totals of the two
+// scans of an event, the two selections and the codes of a selection by all
+// waves, the cell's gas state, the per-cell FP32 factors and the outcome
 // parameters
-struct TeamScratch {
-  double tot[2][8];
-  Cand cand[2][4];
-  Gas gas;
+struct alignas(16) TeamScratch {
+  double tot_i[8], tot_j[8];
+  TeamCand ci, cj;
+  int code[4];
   CellF cf;
   OutcomeConst oc;
+  Gas gas;
 };
 
 // LDS bytes of one particle record in rate precision RT
