@@ -18,6 +18,21 @@
 
 namespace mcd {
 
+// A condition as a lane mask in a general SGPR pair.  A select by VCC has a
+// short encoding, and one of those directly after another of the same wave
+// takes 23 cycles on gfx950 instead of 5 (measured; three in a row are not
+// hidden by three waves per SIMD either); a select by any other pair takes the
+// long encoding, which has no such stall.  The empty asm, which clobbers VCC,
+// keeps the mask in another pair.
+__device__ __forceinline__ uint64_t lane_mask(bool c) {
+  uint64_t m = __builtin_amdgcn_ballot_w64(c);
+  asm("" : "+s"(m) : : "vcc");
+  return m;
+}
+__device__ __forceinline__ float lane_sel(uint64_t m, float a, float b) {
+  return __builtin_amdgcn_inverse_ballot_w64(m) ? a : b;
+}
+
 // physical constants, CGS
 constexpr double kBoltz = 1.380649e-16;
 constexpr double kMassH = 1.6735575e-24;
@@ -426,11 +441,11 @@ __device__ inline RT pair_kernel(const PairConst<RT> &c, const Rec<RT> &x, const
 // 2 ((y_a + eps)/(1 + y_a) + eps^3) / ((1 + eps)(y_a + eps)) --, fused
 // multiply-adds for the quadrature sum, sqrt(pi) folded into the radii.
 //
-// BRANCH: the grouping factors behind a (uniform) test of dm_max, which ends
-// the block of every pair; the row-sum build's blocks of up to 16 pairs run
-// faster so (row sums of 4096 cells of 64 - 1024 particles: 679 against 759 us),
-// the events' straight code without it (the batched workload: 10.9 against
-// 11.6 ms).
+// BRANCH (the row-sum build): the grouping factors behind a (uniform) test of
+// dm_max, which ends the block of every pair; the build's blocks of up to 16
+// pairs run faster so (row sums of 4096 cells of 64 - 1024 particles: 679
+// against 759 us), the events' straight code without it (the batched workload:
+// 10.9 against 11.6 ms).
 template <bool BRANCH = false>
 __device__ inline void pair_rates_all(const PairConst<float> &c, const Rec<float> &x,
                                       const Rec<float> &y, float &dv, float &rxy, float &ryx) {
@@ -441,12 +456,21 @@ __device__ inline void pair_rates_all(const PairConst<float> &c, const Rec<float
   // deferred into the regime choice, a second wait on LDS per pair
   if constexpr (BRANCH) asm volatile("" ::"v"(x.h), "v"(x.q1), "v"(y.h), "v"(y.q1));
   float dv2 = c.cBM * (x.im + y.im);
+  // selects: by masks in the build's dense pairs (row sums of the cells above:
+  // 627 against 671 us), left to the compiler in the events' chain, where the
+  // masks' longer path costs what the stall does
   const bool xb = x.St > y.St;
-  const float St1 = xb ? x.St : y.St;
-  const float ist1 = xb ? x.ist : y.ist;
+  uint64_t xm = 0;
+  if constexpr (BRANCH) xm = lane_mask(xb);
+  auto sel = [&](float a, float b) __attribute__((always_inline)) {
+    if constexpr (BRANCH) return lane_sel(xm, a, b);
+    return xb ? a : b;
+  };
+  const float St1 = sel(x.St, y.St);
+  const float ist1 = sel(x.ist, y.ist);
   // h = St^2 / (St + St_eta) grows with St: the larger-St particle has the larger h
   const float hd = fabsf(x.h - y.h);
-  const float eps = (xb ? y.St : x.St) * ist1;
+  const float eps = sel(y.St, x.St) * ist1;
   const float ye = ya + eps;
   const float rd = __builtin_amdgcn_rcpf((1.0f + eps) * ye);
   const float tiny = (1.0f - eps) * (ye * rd) * hd;
@@ -457,7 +481,11 @@ __device__ inline void pair_rates_all(const PairConst<float> &c, const Rec<float
   // arithmetic into per-regime blocks (which serialise a wave's pairs)
   float tn = tiny, it = inter;
   asm("" : "+v"(tn), "+v"(it));
-  const float turb = St1 < c.St_eta ? tn : (St1 < 1.0f ? it : heavy);
+  float turb;
+  if constexpr (BRANCH)
+    turb = lane_sel(lane_mask(St1 < c.St_eta), tn, lane_sel(lane_mask(St1 < 1.0f), it, heavy));
+  else
+    turb = St1 < c.St_eta ? tn : (St1 < 1.0f ? it : heavy);
   dv2 = fmaf(c.Vg2, turb, dv2);
   float d = x.vr - y.vr;
   dv2 = fmaf(d, d, dv2);
