@@ -796,9 +796,10 @@ mcd_status mcd_sigma_hist(mcd_ctx *c, const double *r_edges, int32_t n_rb, const
   MCD_HIP(c, hipMemcpyAsync(c->d_edges, c->h_edges.data(), ne * sizeof(double),
                             hipMemcpyHostToDevice, c->stream));
   const double *re = c->d_edges, *me = c->d_edges + n_rb + 1;
+  // scratch: the radix sort's keys and values, which no binning reads before writing them
   hipError_t e = launch_sigma_hist(c->part.r, c->part.m, c->part.M, c->part.active, c->part.n, re,
                                    n_rb, me, n_mb, c->prm.column ? 1 : 0, sigma, count, c->cus,
-                                   c->stream);
+                                   c->ws + c->L.k32[0], c->L.flag - c->L.k32[0], c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "sigma_hist");
   return MCD_OK;
 }
