@@ -28,7 +28,7 @@
  *    fixes allocate at that call and free in mcd_free: the gas grid's nodes
  *    (mcd_set_gas_grid) and the snapshot staging (mcd_snapshot, first call
  *    or a larger field set).
- *  - Largest cell: 2048 particles in the mixed form, 1536 in FP64 (a
+ *  - Largest cell: 2048 particles in the mixed form, 1536 in FP64 (the
  *    four-wave team's particle records must fit the 160 KB of LDS); larger
  *    cells are rejected with MCD_EINVAL.
  *  - Every function returns an mcd_status; no C++ exception crosses the ABI.

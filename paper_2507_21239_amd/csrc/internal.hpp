@@ -95,10 +95,11 @@ struct alignas(16) TeamScratch {
   Gas gas;
 };
 
-// LDS bytes of one particle record in rate precision RT
+// LDS bytes of one particle record in rate precision RT: twelve values in
+// FP32; nine in FP64, which forms one again and does not read two
 template <typename RT>
 constexpr size_t rec_bytes() {
-  return 12 * sizeof(RT);
+  return sizeof(RT) == 8 ? 9 * sizeof(RT) : 12 * sizeof(RT);
 }
 
 // partner-sum exchange of a four-wave FP32 team's row-sum build:
@@ -120,12 +121,13 @@ constexpr size_t region_bytes(int cap, int waves) {
   return xbuf_offset<RT>(cap) + (sizeof(RT) == 4 && waves == 4 ? kXbufBytes : 0);
 }
 
-// largest FP64 cell: a four-wave team's region of 96-byte records and its
-// scratch must fit the 160 KB of LDS (the FP32 form's 48-byte records fit
-// kMaxCell)
+// largest FP64 cell, and the largest of a one-wave FP64 team: limits of the
+// interface (72-byte records would leave room for a little more); the FP32
+// form's 48-byte records fit kMaxCell
 constexpr int kMaxCellFp64 = 1536;
+constexpr int kSmallCapFp64 = 384;
+static_assert(4 * region_bytes<double>(kSmallCapFp64, 1) <= 160 * 1024, "kSmallCapFp64 fits");
 static_assert(region_bytes<double>(kMaxCellFp64, 4) <= 160 * 1024, "FP64 cells of kMaxCellFp64 fit");
-static_assert(region_bytes<double>(kMaxCellFp64 + 256, 4) > 160 * 1024, "and no larger ones");
 static_assert(region_bytes<float>(kMaxCell, 4) <= 160 * 1024, "FP32 cells of kMaxCell fit");
 
 // zero the device state and the plan (a new context, or a context-free
@@ -142,6 +144,7 @@ inline bool lds_caps(int precision, int schedule, int max_big, int max_small, in
   const int plain_cap = (max_cell + 255) / 256 * 256;
   if (schedule == 0) big_cap = plain_cap > 256 ? plain_cap : 256;  // one team per cell
   const bool f64 = precision == 0;
+  if (f64 && (big_cap > kMaxCellFp64 || (schedule != 0 && small_cap > kSmallCapFp64))) return false;
   const size_t lds_big = f64 ? region_bytes<double>(big_cap, 4) : region_bytes<float>(big_cap, 4);
   const size_t lds_small =
       4 * (f64 ? region_bytes<double>(small_cap, 1) : region_bytes<float>(small_cap, 1));
