@@ -20,14 +20,15 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libmcd.so")
-SOURCES = ["collide_batched.hip", "collide_batched_prob.hip", "collide_ilp.hip", "collide_ilp3.hip",
-           "collide_plain.hip", "collide_plain_prob.hip", "capi.hip", "collide.hip", "binning.hip", "plan.hip", "transport.hip",
-           "diagnostics.hip", "noalloc.hip"]
+SOURCES = ["collide_batched.hip", "collide_batched_prob.hip", "collide_fp64.hip", "collide_ilp.hip",
+           "collide_ilp3.hip", "collide_plain.hip", "collide_plain_prob.hip", "capi.hip", "collide.hip",
+           "binning.hip", "plan.hip", "transport.hip", "diagnostics.hip", "noalloc.hip"]
 # per-file flags on top of CFLAGS
 ILP = ["-mllvm", "--amdgpu-sched-strategy=max-ilp"]
 SINK = ["-mllvm", "-sink-insts-to-avoid-spills=1"]
-EXTRA = {"collide_ilp.hip": ILP, "collide_ilp3.hip": ILP + SINK, "collide_batched.hip": SINK,
-         "collide_batched_prob.hip": SINK, "collide_plain.hip": SINK, "collide_plain_prob.hip": SINK}
+EXTRA = {"collide_fp64.hip": SINK, "collide_ilp.hip": ILP, "collide_ilp3.hip": ILP + SINK,
+         "collide_batched.hip": SINK, "collide_batched_prob.hip": SINK, "collide_plain.hip": SINK,
+         "collide_plain_prob.hip": SINK}
 ARCH = os.environ.get("MCD_ARCH", "gfx950")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

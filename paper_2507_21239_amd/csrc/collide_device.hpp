@@ -20,11 +20,11 @@
 // packed vectors indexed by s = q*64nw + t (slot q of lane t), so a wave reads
 // consecutive 16-byte words.  Row sums (FP64), the per-event row values,
 // masses and particle indices stay in registers of the owning lane; masses go
-// back to HBM once, when the cell is done.  In the FP32 form the starting row
-// sums evaluate each unordered pair once (build_rows_pairwise*); the FP64 form
-// sums every row in canonical order.  The batched kernel carries the
-// composition mix and the event log only in the variant launched for runs
-// that use them.
+// back to HBM once, when the cell is done.  The starting row sums evaluate each
+// unordered pair once (build_rows_pairwise*) in the FP32 fast path and in FP64,
+// both up to four slots per lane; otherwise every row is summed in canonical
+// order.  The batched kernel carries the composition mix and the event log only
+// in the variant launched for runs that use them.
 //
 // The cell body and the kernel templates; collide_launch.hpp launches them.
 #pragma once
@@ -124,8 +124,24 @@ struct PairEval<float, true> {
   }
 };
 
+// two partner sums on their way to another wave
+template <typename RT>
+struct alignas(2 * sizeof(RT)) Pair2 {
+  RT x, y;
+};
+__device__ inline void build_pair(const PairConst<float> &c, const Rec<float> &x,
+                                  const Rec<float> &y, float &rxy, float &ryx) {
+  float dv;
+  pair_rates_all<true>(c, x, y, dv, rxy, ryx);
+}
+__device__ inline void build_pair(const PairConst<double> &c, const Rec<double> &x,
+                                  const Rec<double> &y, double &rxy, double &ryx) {
+  double dv;
+  PairEval<double, false>::run(c, x, y, dv, rxy, ryx);
+}
+
 // ---------------------------------------------------------------------------
-// row sums of a one-wave FP32 cell, each unordered pair evaluated once
+// row sums of a one-wave cell, each unordered pair evaluated once
 // ---------------------------------------------------------------------------
 // Lane l holds slots (q, l), q < K.  Step 0 pairs the lane's own slots; step
 // d = 1..32 pairs lane l with lane (l + d) mod 64 (at d = 32 only lanes below
@@ -134,17 +150,17 @@ struct PairEval<float, true> {
 // lane down after every step (DPP wave rotation), so that the accumulator of
 // lane X is always held by the lane currently paired with X; after step 32 it
 // sits at lane X - 32 and returns with one exchange of the wave's halves.
-// Sums are in FP32, in an order that differs from the canonical one; slots
-// past the cell's particles get 0.
-template <int KMAX>
-__device__ inline void build_rows_pairwise(const RecStore<float> &R, const PairConst<float> &pc,
+// Sums are in the rate precision, in an order that differs from the members';
+// slots past the cell's particles get 0.
+template <typename RT, int KMAX>
+__device__ inline void build_rows_pairwise(const RecStore<RT> &R, const PairConst<RT> &pc,
                                            int K, int lane, int n, double r[KMAX]) {
-  Rec<float> mine[KMAX];
-  float acc[KMAX], pacc[KMAX];
+  Rec<RT> mine[KMAX];
+  RT acc[KMAX], pacc[KMAX];
 #pragma unroll
   for (int q = 0; q < KMAX; ++q) {
-    acc[q] = 0.0f;
-    pacc[q] = 0.0f;
+    acc[q] = (RT)0;
+    pacc[q] = (RT)0;
     if (q < K) mine[q] = R.load(q * 64 + lane);
   }
 #pragma unroll
@@ -152,8 +168,8 @@ __device__ inline void build_rows_pairwise(const RecStore<float> &R, const PairC
 #pragma unroll
     for (int J = I; J < KMAX; ++J) {
       if (J < K) {
-        float dv, rxy, ryx;
-        pair_rates_all<true>(pc, mine[I], mine[J], dv, rxy, ryx);
+        RT rxy, ryx;
+        build_pair(pc, mine[I], mine[J], rxy, ryx);
         acc[I] += rxy;
         if (J != I) acc[J] += ryx;
       }
@@ -162,7 +178,7 @@ __device__ inline void build_rows_pairwise(const RecStore<float> &R, const PairC
 #pragma unroll 1
   for (int d = 1; d <= 32; ++d) {
     const int c = (lane + d) & 63;
-    Rec<float> pr[KMAX];
+    Rec<RT> pr[KMAX];
 #pragma unroll
     for (int J = 0; J < KMAX; ++J)
       if (J < K) pr[J] = R.load(J * 64 + c);
@@ -172,47 +188,46 @@ __device__ inline void build_rows_pairwise(const RecStore<float> &R, const PairC
 #pragma unroll
       for (int J = 0; J < KMAX; ++J) {
         if (I < K && J < K) {
-          float dv, rxy, ryx;
-          pair_rates_all<true>(pc, mine[I], pr[J], dv, rxy, ryx);
-          acc[I] += take ? rxy : 0.0f;
-          pacc[J] += take ? ryx : 0.0f;
+          RT rxy, ryx;
+          build_pair(pc, mine[I], pr[J], rxy, ryx);
+          acc[I] += take ? rxy : (RT)0;
+          pacc[J] += take ? ryx : (RT)0;
         }
       }
     }
     if (d < 32) {
 #pragma unroll
       for (int J = 0; J < KMAX; ++J)  // lane l takes lane l + 1's accumulators
-        pacc[J] = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(pacc[J]), 0x134,
-                                                             0xf, 0xf, false));
+        pacc[J] = dpp_t<0x134, 0xf, 0xf>(pacc[J]);
     }
   }
 #pragma unroll
   for (int q = 0; q < KMAX; ++q) {
-    const float home = __shfl_xor(pacc[q], 32, 64);
+    const RT home = __shfl_xor(pacc[q], 32, 64);
     r[q] = (q < K && lane * K + q < n) ? (double)(acc[q] + home) : 0.0;
   }
 }
 
-// Four-wave FP32 teams: the same scheme over the team's 256 lanes.  Wave a
+// Four-wave teams: the same scheme over the team's 256 lanes.  Wave a
 // first pairs its own lanes as above; then in phases p = 1..3 it pairs lane
 // l with lane (l + d) mod 64 of wave b = (a + p) mod 4, for d = 0..31 if
 // a < b and d = 1..32 if a > b (the two waves of a pair split the 64 lane
 // offsets between them).  After each phase the partner accumulators, which
 // moved one lane per step as above, go to wave b through the exchange buffer
 // in two rounds of two slots (a barrier after each write and before reuse).
-template <int KMAX>
-__device__ inline void build_rows_pairwise_team(const RecStore<float> &R, const PairConst<float> &pc,
-                                                int K, int wave, int lane, int n, float2 *xbuf,
+template <typename RT, int KMAX>
+__device__ inline void build_rows_pairwise_team(const RecStore<RT> &R, const PairConst<RT> &pc,
+                                                int K, int wave, int lane, int n, Pair2<RT> *xbuf,
                                                 double r[KMAX]) {
   static_assert(KMAX % 2 == 0, "partner sums go over in pairs of slots");
   constexpr int TL = 256;
   const int own = wave * 64;
-  Rec<float> mine[KMAX];
-  float acc[KMAX], pacc[KMAX];
+  Rec<RT> mine[KMAX];
+  RT acc[KMAX], pacc[KMAX];
 #pragma unroll
   for (int q = 0; q < KMAX; ++q) {
-    acc[q] = 0.0f;
-    pacc[q] = 0.0f;
+    acc[q] = (RT)0;
+    pacc[q] = (RT)0;
     if (q < K) mine[q] = R.load(q * TL + own + lane);
   }
 #pragma unroll
@@ -220,8 +235,8 @@ __device__ inline void build_rows_pairwise_team(const RecStore<float> &R, const 
 #pragma unroll
     for (int J = I; J < KMAX; ++J) {
       if (J < K) {
-        float dv, rxy, ryx;
-        pair_rates_all<true>(pc, mine[I], mine[J], dv, rxy, ryx);
+        RT rxy, ryx;
+        build_pair(pc, mine[I], mine[J], rxy, ryx);
         acc[I] += rxy;
         if (J != I) acc[J] += ryx;
       }
@@ -231,7 +246,7 @@ __device__ inline void build_rows_pairwise_team(const RecStore<float> &R, const 
 #pragma unroll 1
   for (int d = 1; d <= 32; ++d) {
     const int c = (lane + d) & 63;
-    Rec<float> pr[KMAX];
+    Rec<RT> pr[KMAX];
 #pragma unroll
     for (int J = 0; J < KMAX; ++J)
       if (J < K) pr[J] = R.load(J * TL + own + c);
@@ -241,24 +256,23 @@ __device__ inline void build_rows_pairwise_team(const RecStore<float> &R, const 
 #pragma unroll
       for (int J = 0; J < KMAX; ++J) {
         if (I < K && J < K) {
-          float dv, rxy, ryx;
-          pair_rates_all<true>(pc, mine[I], pr[J], dv, rxy, ryx);
-          acc[I] += take ? rxy : 0.0f;
-          pacc[J] += take ? ryx : 0.0f;
+          RT rxy, ryx;
+          build_pair(pc, mine[I], pr[J], rxy, ryx);
+          acc[I] += take ? rxy : (RT)0;
+          pacc[J] += take ? ryx : (RT)0;
         }
       }
     }
     if (d < 32) {
 #pragma unroll
       for (int J = 0; J < KMAX; ++J)
-        pacc[J] = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(pacc[J]), 0x134,
-                                                             0xf, 0xf, false));
+        pacc[J] = dpp_t<0x134, 0xf, 0xf>(pacc[J]);
     }
   }
 #pragma unroll
   for (int q = 0; q < KMAX; ++q) {
     acc[q] += __shfl_xor(pacc[q], 32, 64);
-    pacc[q] = 0.0f;
+    pacc[q] = (RT)0;
   }
   // the lanes of the other three waves
 #pragma unroll 1
@@ -268,7 +282,7 @@ __device__ inline void build_rows_pairwise_team(const RecStore<float> &R, const 
 #pragma unroll 1
     for (int st = 0; st < 32; ++st) {
       const int c = (lane + d0 + st) & 63;
-      Rec<float> pr[KMAX];
+      Rec<RT> pr[KMAX];
 #pragma unroll
       for (int J = 0; J < KMAX; ++J)
         if (J < K) pr[J] = R.load(J * TL + b * 64 + c);
@@ -277,8 +291,8 @@ __device__ inline void build_rows_pairwise_team(const RecStore<float> &R, const 
 #pragma unroll
         for (int J = 0; J < KMAX; ++J) {
           if (I < K && J < K) {
-            float dv, rxy, ryx;
-            pair_rates_all<true>(pc, mine[I], pr[J], dv, rxy, ryx);
+            RT rxy, ryx;
+            build_pair(pc, mine[I], pr[J], rxy, ryx);
             acc[I] += rxy;
             pacc[J] += ryx;
           }
@@ -287,23 +301,22 @@ __device__ inline void build_rows_pairwise_team(const RecStore<float> &R, const 
       if (st < 31) {
 #pragma unroll
         for (int J = 0; J < KMAX; ++J)
-          pacc[J] = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(pacc[J]), 0x134,
-                                                               0xf, 0xf, false));
+          pacc[J] = dpp_t<0x134, 0xf, 0xf>(pacc[J]);
       }
     }
     // lane l now holds the sums of lane (l + d0 + 31) mod 64 of wave b; they
     // go over in two rounds of two slots
 #pragma unroll
     for (int h = 0; h < KMAX; h += 2) {
-      xbuf[b * 64 + ((lane + d0 + 31) & 63)] = make_float2(pacc[h], pacc[h + 1]);
+      xbuf[b * 64 + ((lane + d0 + 31) & 63)] = Pair2<RT>{pacc[h], pacc[h + 1]};
       block_lds_sync();
-      const float2 in = xbuf[own + lane];
+      const Pair2<RT> in = xbuf[own + lane];
       acc[h] += in.x;
       acc[h + 1] += in.y;
       block_lds_sync();
     }
 #pragma unroll
-    for (int q = 0; q < KMAX; ++q) pacc[q] = 0.0f;
+    for (int q = 0; q < KMAX; ++q) pacc[q] = (RT)0;
   }
   const int tl = own + lane;
 #pragma unroll
@@ -1121,18 +1134,20 @@ __device__ __forceinline__ void process_cell(const CollideArgs &A, int cell, cha
   team_sync<NW>();
 
   // ---- row sums r_i = sum_k r_ik ------------------------------------------
-  // The FP32 form evaluates each unordered pair once (build_rows_pairwise,
-  // build_rows_pairwise_team).  Otherwise partners k = 0..n-1 are read once per
+  // The FP32 fast path and FP64 up to four slots per lane evaluate each
+  // unordered pair once (build_rows_pairwise, build_rows_pairwise_team; batched
+  // FP64 workload, 250 events: 2.72 against 3.35 ms; own slots one after the
+  // other, a quarter of the code: 2.73, its row sums alone 15% slower).  Otherwise partners k = 0..n-1 are read once per
   // group of G own slots and paired with each of them (independent
   // evaluations), and each row adds its terms in canonical order.
   double r[KMAX];
   bool built = false;
-  if constexpr (sizeof(RT) == 4 && FAST && KMAX == 4) {
+  if constexpr ((sizeof(RT) == 8 || FAST) && KMAX == 4) {
     if (nw == 1)
-      build_rows_pairwise<KMAX>(R, pc, K, lane, n, r);
+      build_rows_pairwise<RT, KMAX>(R, pc, K, lane, n, r);
     else
-      build_rows_pairwise_team<KMAX>(R, pc, K, wave, lane, n,
-                                     (float2 *)(base + xbuf_offset<RT>(cap)), r);
+      build_rows_pairwise_team<RT, KMAX>(R, pc, K, wave, lane, n,
+                                         (Pair2<RT> *)(base + xbuf_offset<RT>(cap)), r);
     built = true;
   }
   if (!built) {

@@ -8,7 +8,7 @@
 
 namespace mcd {
 
-// defined in collide_ilp.hip and collide_ilp3.hip
+// defined in collide_ilp.hip, collide_ilp3.hip and collide_fp64.hip
 extern template __global__ void collide_batched<float, 4, true, false, false, kTimeLimited>(
     CollideArgs A);
 extern template __global__ void collide_batched<float, 4, true, false, true, kTimeLimited>(

@@ -102,11 +102,14 @@ constexpr size_t rec_bytes() {
   return sizeof(RT) == 8 ? 9 * sizeof(RT) : 12 * sizeof(RT);
 }
 
-// partner-sum exchange of a four-wave FP32 team's row-sum build:
-// [wave][lane] pairs of floats (two slots per round), after the team scratch.
-// 2 KB keeps a 1024-particle team region within the LDS of four 256-particle
-// one-wave regions, so the exchange costs no occupancy
-constexpr size_t kXbufBytes = 4 * 64 * 2 * sizeof(float);
+// partner-sum exchange of a four-wave team's row-sum build: [wave][lane] pairs
+// of sums (two slots per round), after the team scratch.  Its 2 KB in FP32 keep
+// a 1024-particle team region within the LDS of four 256-particle one-wave
+// regions; in FP64 (4 KB) two such regions still share a CU
+template <typename RT>
+constexpr size_t xbuf_bytes() {
+  return 4 * 64 * 2 * sizeof(RT);
+}
 
 // byte offset of the exchange buffer in a team region holding `cap` particles
 template <typename RT>
@@ -115,10 +118,10 @@ constexpr size_t xbuf_offset(int cap) {
 }
 
 // LDS bytes of one team region holding `cap` particles (16-byte multiple);
-// four-wave FP32 teams add the exchange buffer
+// four-wave teams add the exchange buffer
 template <typename RT>
 constexpr size_t region_bytes(int cap, int waves) {
-  return xbuf_offset<RT>(cap) + (sizeof(RT) == 4 && waves == 4 ? kXbufBytes : 0);
+  return xbuf_offset<RT>(cap) + (waves == 4 ? xbuf_bytes<RT>() : 0);
 }
 
 // largest FP64 cell, and the largest of a one-wave FP64 team: limits of the
@@ -128,6 +131,7 @@ constexpr int kMaxCellFp64 = 1536;
 constexpr int kSmallCapFp64 = 384;
 static_assert(4 * region_bytes<double>(kSmallCapFp64, 1) <= 160 * 1024, "kSmallCapFp64 fits");
 static_assert(region_bytes<double>(kMaxCellFp64, 4) <= 160 * 1024, "FP64 cells of kMaxCellFp64 fit");
+static_assert(2 * region_bytes<double>(1024, 4) <= 160 * 1024, "two FP64 teams of 1024 share a CU");
 static_assert(region_bytes<float>(kMaxCell, 4) <= 160 * 1024, "FP32 cells of kMaxCell fit");
 
 // zero the device state and the plan (a new context, or a context-free
