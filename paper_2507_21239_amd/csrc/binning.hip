@@ -41,8 +41,9 @@ __device__ inline uint64_t key_bits(double x) {
 // ---------------------------------------------------------------------------
 // active count and range of the r bit patterns
 // ---------------------------------------------------------------------------
-// per-workgroup partials {min, max, count}, then one workgroup combines them
-// (no atomics: a few thousand 64-bit atomics on one address serialise)
+// per-workgroup partials {min, max, count}, which every workgroup of the next
+// kernel combines for itself (no atomics: a few thousand 64-bit atomics on one
+// address serialise; and no launch of 4 us for 256 values)
 __device__ inline void minmax_wave(uint64_t &lo, uint64_t &hi, uint64_t &cnt) {
   for (int off = 32; off > 0; off >>= 1) {
     const uint64_t l2 = __shfl_xor(lo, off, 64), h2 = __shfl_xor(hi, off, 64);
@@ -72,7 +73,7 @@ __device__ inline void minmax_block(uint64_t &lo, uint64_t &hi, uint64_t &cnt) {
   }
 }
 
-__global__ __launch_bounds__(256) void k_minmax_part(const double *__restrict__ r,
+__global__ __launch_bounds__(1024) void k_minmax_part(const double *__restrict__ r,
                                                      const uint8_t *__restrict__ active,
                                                      int64_t N, uint64_t *part) {
   uint64_t lo = ~0ull, hi = 0ull, cnt = 0;
@@ -93,41 +94,46 @@ __global__ __launch_bounds__(256) void k_minmax_part(const double *__restrict__ 
   }
 }
 
-__global__ __launch_bounds__(1024) void k_minmax_final(const uint64_t *part, int n_part,
-                                                       BinState *bs, DevState *st) {
+// the workgroup's (256 threads) view of the partials
+__device__ inline BinState combine_parts(const uint64_t *__restrict__ part, int n_part) {
+  static_assert(kMinmaxParts <= 256, "one partial per thread");
+  const int k = threadIdx.x;
   uint64_t lo = ~0ull, hi = 0ull, cnt = 0;
-  for (int k = threadIdx.x; k < n_part; k += blockDim.x) {
-    lo = part[3 * k] < lo ? part[3 * k] : lo;
-    hi = part[3 * k + 1] > hi ? part[3 * k + 1] : hi;
-    cnt += part[3 * k + 2];
+  if (k < n_part) {
+    lo = part[3 * k];
+    hi = part[3 * k + 1];
+    cnt = part[3 * k + 2];
   }
   minmax_block(lo, hi, cnt);
-  if (threadIdx.x == 0) {
-    bs->min_bits = lo;
-    bs->max_bits = hi;
-    bs->count = (uint32_t)cnt;
-    st->n_active = (int32_t)cnt;
-  }
+  return BinState{lo, hi, (uint32_t)cnt, 0u};
 }
 
-__device__ inline int key_shift(const BinState *bs) {
-  const uint64_t span = bs->max_bits - bs->min_bits;
+__device__ inline int key_shift(const BinState &bs) {
+  const uint64_t span = bs.max_bits - bs.min_bits;
   const int bits = span ? 64 - __builtin_clzll(span) : 0;
   return bits > 31 ? bits - 31 : 0;
 }
 
 // 32-bit keys of one radix tile, and the tile's histogram of the first
-// digit (the first pass needs no histogram kernel of its own); elements in
-// the tile order of the radix kernels
+// digit (the first pass needs no histogram kernel of its own).  The first
+// workgroup leaves the active count and readies the state for the collision
+// launch and the end of the step
 __global__ __launch_bounds__(256) void k_keys_r32_hist(const double *__restrict__ r,
                                                        const uint8_t *__restrict__ active, int64_t N,
-                                                       const BinState *bs, uint32_t *keys,
+                                                       const uint64_t *part, int n_part,
+                                                       DevState *st, uint32_t *keys,
                                                        int32_t *vals, uint32_t *hist, int tiles) {
   __shared__ uint32_t h[256];
   h[threadIdx.x] = 0u;
-  __syncthreads();
+  const BinState bs = combine_parts(part, n_part);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    st->n_active = (int32_t)bs.count;
+    st->big_head = 0;
+    st->small_head = 0;
+    st->bin_step = st->step;
+  }
   const int sh = key_shift(bs);
-  const uint64_t lo = bs->min_bits;
+  const uint64_t lo = bs.min_bits;
   const int64_t base = (int64_t)blockIdx.x * kRadixTile;
 #pragma unroll
   for (int it = 0; it < kRadixItems; ++it) {
@@ -844,12 +850,11 @@ hipError_t launch_binning(const Model &P, int n_r, int n_z, const double *r, con
   const unsigned g1 = (unsigned)((N + 255) / 256);
   hipError_t e;
   // 1. rank by (r, index)
-  const unsigned n_part = std::min<unsigned>(g1, kMinmaxParts);
-  k_minmax_part<<<n_part, 256, 0, s>>>(r, active, N, b.part);
-  k_minmax_final<<<1, 1024, 0, s>>>(b.part, (int)n_part, b.bs, state);
+  const unsigned n_part = (unsigned)std::min<int64_t>((N + 1023) / 1024, kMinmaxParts);
+  k_minmax_part<<<n_part, 1024, 0, s>>>(r, active, N, b.part);
   const int tiles = radix_tiles(N);
-  k_keys_r32_hist<<<tiles, kRadixThreads, 0, s>>>(r, active, N, b.bs, b.k32[0], b.vals[0], b.hist,
-                                                  tiles);
+  k_keys_r32_hist<<<tiles, kRadixThreads, 0, s>>>(r, active, N, b.part, (int)n_part, state,
+                                                  b.k32[0], b.vals[0], b.hist, tiles);
   int cur = 0;
   for (int sh = 0; sh < 32; sh += 8)
     if ((e = radix_pass<uint32_t>(b.k32, b.vals, b.hist, b.digit_tot, cur, N, sh, s, sh == 0)) !=

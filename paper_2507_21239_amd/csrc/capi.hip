@@ -31,7 +31,7 @@ struct Layout {
   size_t big, small, hist, cursor;            // cell lists and their planning
   size_t mbak, cbak;                          // tuning backups of m and comp
   size_t edges;                               // histogram edges
-  size_t k32[2], vals[2], flag, bs, part, by_r, hist_r, digit, k64[2], zone;  // binning
+  size_t k32[2], vals[2], flag, part, by_r, hist_r, digit, k64[2], zone;  // binning
   size_t total;
   int64_t cells_adaptive, cells_cap;
   int tiles;
@@ -70,7 +70,6 @@ Layout layout_for(const mcd_params &p, int64_t N) {
     L.vals[k] = take(n * sizeof(int32_t));
   }
   L.flag = take(n);
-  L.bs = take(sizeof(BinState));
   L.part = take((size_t)3 * kMinmaxParts * sizeof(uint64_t));
   L.by_r = take(n * sizeof(int32_t));
   L.hist_r = take((size_t)256 * L.tiles * sizeof(uint32_t));
@@ -276,7 +275,6 @@ void carve(mcd_ctx *c) {
     b.keys[k] = L.global_z ? (uint64_t *)(w + L.k64[k]) : nullptr;
   }
   b.flag = (uint8_t *)(w + L.flag);
-  b.bs = (BinState *)(w + L.bs);
   b.part = (uint64_t *)(w + L.part);
   b.by_r = (int32_t *)(w + L.by_r);
   b.zone = L.global_z ? (int32_t *)(w + L.zone) : nullptr;
@@ -374,13 +372,14 @@ mcd_status enqueue_step(mcd_ctx *c, double dt, int64_t max_events, hipStream_t s
   if (c->prm.flags & COAG) {
     hipError_t e = launch_collide(collide_args(c, dt, max_events), c->prm.precision,
                                   c->prm.schedule, c->n_cells, c->max_cell,
-                                  c->grid_per_cu * c->cus, s);
+                                  c->grid_per_cu * c->cus, s, c->adaptive);
     if (e != hipSuccess) return hip_fail(c, e, "collide");
   }
   if (c->adaptive && transport_on(c)) {
     hipError_t e = launch_transport(c->model, c->part.r, c->part.z, c->part.m, c->part.active,
                                     c->part.n, dt, c->d_state, s);
     if (e != hipSuccess) return hip_fail(c, e, "transport");
+    return MCD_OK;
   }
   hipError_t e = launch_finish_step(c->d_state, dt, s);
   if (e != hipSuccess) return hip_fail(c, e, "finish_step");

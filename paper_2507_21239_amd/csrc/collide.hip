@@ -14,11 +14,6 @@ __global__ void reset_queues(DevState *st) {
   st->small_head = 0;
 }
 
-hipError_t launch_reset_queues(DevState *st, hipStream_t s) {
-  reset_queues<<<1, 1, 0, s>>>(st);
-  return hipGetLastError();
-}
-
 // ---------------------------------------------------------------------------
 // test path: the full rate matrix of one cell, from the same records and
 // pair code as the collision kernel
@@ -60,7 +55,7 @@ __global__ __launch_bounds__(256) void rates_cell(CollideArgs A, int cell, doubl
 }
 
 hipError_t launch_collide(const CollideArgs &a, int precision, int schedule, int n_cells,
-                          int max_cell, int grid_override, hipStream_t s) {
+                          int max_cell, int grid_override, hipStream_t s, bool queues_clear) {
   // slots per lane: four-wave teams hold big_cap particles, single waves
   // small_cap; kernels exist for up to 4 and up to 8
   const int k_big = (a.big_cap + 255) / 256, k_small = (a.small_cap + 63) / 64;
@@ -72,6 +67,11 @@ hipError_t launch_collide(const CollideArgs &a, int precision, int schedule, int
   if (schedule == 0)
     return prob ? launch_plain<true>(a, precision, n_cells, wide, s)
                 : launch_plain<false>(a, precision, n_cells, wide, s);
+  if (!queues_clear) {
+    reset_queues<<<1, 1, 0, s>>>(a.state);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   return prob ? launch_batched<true>(a, precision, wide, grid_override, s)
               : launch_batched<false>(a, precision, wide, grid_override, s);
 }

@@ -18,8 +18,6 @@ extern template __global__ void collide_batched<float, 4, true, false, false, kF
 extern template __global__ void collide_batched<double, 4, false, false, false, kFixedCount>(
     CollideArgs A);
 
-hipError_t launch_reset_queues(DevState *st, hipStream_t s);
-
 template <typename Kern>
 inline hipError_t prepare(Kern kern, size_t lds) {
   if (lds > 64 * 1024)
@@ -57,8 +55,6 @@ inline hipError_t run_batched(const CollideArgs &a, int grid_override, hipStream
   // device; workgroups beyond the work exit at their first queue pop)
   int grid = per_cu * cus;
   if (grid_override > 0) grid = grid_override;
-  hipError_t er = launch_reset_queues(a.state, s);
-  if (er != hipSuccess) return er;
   kern<<<grid, 256, lds, s>>>(a);
   return hipGetLastError();
 }

@@ -15,7 +15,7 @@ struct DevState {
   int32_t n_active;       // active particles after binning
   int32_t big_head;       // persistent work queues
   int32_t small_head;
-  int32_t pad0;
+  uint32_t bin_step;      // step index when the grid was last binned
   double t_sim;           // simulated time
   unsigned long long events;
   unsigned long long outcomes[4];
@@ -175,18 +175,23 @@ const char *contextless_error();
 // planning of the batched lists (plan.hip): an explicit grid is validated
 // (member ranges, cells of at most `bound` particles, member indices below
 // N) and its cells sorted by size; a uniform grid takes every cell in order
+// fresh: the device state is zeroed first and takes the step index *fresh
+// (a context-free step)
 hipError_t launch_plan_explicit(const int32_t *cell_start, const int32_t *order, int32_t nc,
                                 int64_t N, int32_t bound, int32_t small_max, PlanBuffers pb,
-                                DevState *state, hipStream_t s);
+                                DevState *state, hipStream_t s, const uint32_t *fresh = nullptr);
 hipError_t launch_plan_uniform(int32_t nc, int32_t size, int32_t small_max, PlanBuffers pb,
                                hipStream_t s);
 
-// launchers (collide.hip)
+// launchers (collide.hip); queues_clear: the work queues' heads are zero, set
+// by the binning or the state's clearing in front of this launch
 hipError_t launch_collide(const CollideArgs &a, int precision, int schedule, int n_cells,
-                          int max_cell, int grid_override, hipStream_t s);
+                          int max_cell, int grid_override, hipStream_t s,
+                          bool queues_clear = false);
 hipError_t launch_rates_cell(const CollideArgs &a, int precision, int cell, double *r_out,
                              int64_t ld, double *rowsum_out, hipStream_t s);
-// transport (transport.hip)
+// transport (transport.hip); it also ends the step, as launch_finish_step does
+// for steps without it
 hipError_t launch_transport(const Model &P, double *r, double *z, const double *m,
                             uint8_t *active, int64_t N, double dt, DevState *state,
                             hipStream_t s);
@@ -206,14 +211,13 @@ struct BinState {
 // global radix path
 constexpr int kZoneSortMax = 8192;
 // workgroups of the first reduction over r (partials of 3 words each)
-constexpr int kMinmaxParts = 1024;
+constexpr int kMinmaxParts = 256;
 
 struct BinBuffers {
   uint64_t *keys[2];   // 64-bit keys of the global z path
   uint32_t *k32[2];    // 32-bit keys of the r sort
   int32_t *vals[2];
   uint8_t *flag;       // neighbours with equal r keys but different r
-  BinState *bs;
   uint64_t *part;      // [3 kMinmaxParts] partial {min, max, count}
   int32_t *by_r;       // active particle indices by ascending (r, index)
   int32_t *zone;       // zone of every particle (n_r for inactive)

@@ -125,10 +125,8 @@ extern "C" mcd_status mcd_collide_noalloc(const mcd_params *params, const mcd_pa
   pb.small = (int32_t *)(sc + kOffSmall);
   // the previous call's counters and plan are cleared by a kernel (no memset
   // node, so that the call can be captured in a graph)
-  hipError_t e = launch_clear_state(state, pb.plan, step, s);
-  if (e == hipSuccess)
-    e = launch_plan_explicit(cells->cell_start, cells->order, cells->n_cells, p.n, bound,
-                             kNoallocSmallMax, pb, state, s);
+  hipError_t e = launch_plan_explicit(cells->cell_start, cells->order, cells->n_cells, p.n, bound,
+                                      kNoallocSmallMax, pb, state, s, &step);
   if (e == hipSuccess && (params->flags & COAG)) {
     CollideArgs a{};
     a.P = make_model(*params);
@@ -150,7 +148,7 @@ extern "C" mcd_status mcd_collide_noalloc(const mcd_params *params, const mcd_pa
     a.evlog = nullptr;
     a.log_per_cell = 0;
     a.rowsum_dump = nullptr;
-    e = launch_collide(a, precision, schedule, cells->n_cells, bound, 0, s);
+    e = launch_collide(a, precision, schedule, cells->n_cells, bound, 0, s, true);
   }
   if (e == hipSuccess && counts) {
     k_counts_out<<<1, 1, 0, s>>>(state, counts);

@@ -9,7 +9,8 @@
 // power-law disk), under which the axisymmetric walk keeps tracers
 // distributed like the gas; |z| folded by mirror symmetry; particles inside
 // r_in leave the grid.  One thread per particle,
-// coalesced FP64 loads and stores.
+// coalesced FP64 loads and stores.  The launch also ends the step (one launch
+// of 4 us less a step).
 #include "device_common.hpp"
 #include "internal.hpp"
 
@@ -19,10 +20,14 @@ __global__ __launch_bounds__(256) void transport_kernel(Model P, double *__restr
                                                         double *__restrict__ z,
                                                         const double *__restrict__ m,
                                                         uint8_t *__restrict__ active, int64_t N,
-                                                        double dt, const DevState *st) {
+                                                        double dt, DevState *st) {
   const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const uint32_t step = st->bin_step;  // of the binning in front; st->step moves on here
+  if (k == 0) {
+    st->step = step + 1u;
+    st->t_sim += dt;
+  }
   if (k >= N || !active[k]) return;
-  const uint32_t step = st->step;
   const double rk = P.column ? P.r_col : r[k];
   const double zk = z[k];
   const LocalGas d = local_gas_at(P, rk, zk);
