@@ -72,8 +72,8 @@ hipError_t launch_collide(const CollideArgs &a, int precision, int schedule, int
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  return prob ? launch_batched<true>(a, precision, wide, grid_override, s)
-              : launch_batched<false>(a, precision, wide, grid_override, s);
+  return prob ? launch_batched<true>(a, precision, n_cells, wide, grid_override, s)
+              : launch_batched<false>(a, precision, n_cells, wide, grid_override, s);
 }
 
 hipError_t launch_rates_cell(const CollideArgs &a, int precision, int cell, double *r_out,

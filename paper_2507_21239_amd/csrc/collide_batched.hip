@@ -4,9 +4,9 @@
 namespace mcd {
 
 template <>
-hipError_t launch_batched<false>(const CollideArgs &a, int precision, bool wide, int grid_override,
-                                 hipStream_t s) {
-  return batched_forms<false>(a, precision, wide, grid_override, s);
+hipError_t launch_batched<false>(const CollideArgs &a, int precision, int n_cells, bool wide,
+                                 int grid_override, hipStream_t s) {
+  return batched_forms<false>(a, precision, n_cells, wide, grid_override, s);
 }
 
 }  // namespace mcd

@@ -27,7 +27,7 @@ inline hipError_t prepare(Kern kern, size_t lds) {
 }
 
 template <typename RT, int KMAX, bool FAST, bool PROB>
-inline hipError_t run_batched(const CollideArgs &a, int grid_override, hipStream_t s) {
+inline hipError_t run_batched(const CollideArgs &a, int n_cells, int grid_override, hipStream_t s) {
   const size_t lds = std::max(region_bytes<RT>(a.big_cap, 4), 4 * region_bytes<RT>(a.small_cap, 1));
   // the composition mix and the event log only where they are used
   const bool aux = (a.comp != nullptr && a.P.n_comp > 0) || a.evlog != nullptr;
@@ -51,9 +51,11 @@ inline hipError_t run_batched(const CollideArgs &a, int grid_override, hipStream
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kern, 256, lds);
   if (e != hipSuccess) return e;
   if (per_cu < 1) return hipErrorInvalidConfiguration;
-  // persistent workgroups: as many as fit (the list lengths are on the
-  // device; workgroups beyond the work exit at their first queue pop)
-  int grid = per_cu * cus;
+  // persistent workgroups: as many as fit, and no more than cells (the list
+  // lengths are on the device; workgroups beyond the work exit at their first
+  // queue pop, but starting them costs: a call over 8 cells takes 43 us with 8
+  // workgroups, 73 with 768)
+  int grid = std::min(per_cu * cus, std::max(n_cells, 1));
   if (grid_override > 0) grid = grid_override;
   kern<<<grid, 256, lds, s>>>(a);
   return hipGetLastError();
@@ -77,31 +79,31 @@ inline bool fast_path(const CollideArgs &a, int precision) {
 }
 
 template <bool PROB>
-hipError_t launch_batched(const CollideArgs &a, int precision, bool wide, int grid_override,
-                          hipStream_t s);
+hipError_t launch_batched(const CollideArgs &a, int precision, int n_cells, bool wide,
+                          int grid_override, hipStream_t s);
 template <bool PROB>
 hipError_t launch_plain(const CollideArgs &a, int precision, int n_cells, bool wide, hipStream_t s);
 template <>
-hipError_t launch_batched<false>(const CollideArgs &, int, bool, int, hipStream_t);
+hipError_t launch_batched<false>(const CollideArgs &, int, int, bool, int, hipStream_t);
 template <>
-hipError_t launch_batched<true>(const CollideArgs &, int, bool, int, hipStream_t);
+hipError_t launch_batched<true>(const CollideArgs &, int, int, bool, int, hipStream_t);
 template <>
 hipError_t launch_plain<false>(const CollideArgs &, int, int, bool, hipStream_t);
 template <>
 hipError_t launch_plain<true>(const CollideArgs &, int, int, bool, hipStream_t);
 
 template <bool PROB>
-hipError_t batched_forms(const CollideArgs &a, int precision, bool wide, int grid_override,
-                         hipStream_t s) {
+hipError_t batched_forms(const CollideArgs &a, int precision, int n_cells, bool wide,
+                         int grid_override, hipStream_t s) {
   const bool fast = fast_path(a, precision);
   if (precision == 0)
-    return wide ? run_batched<double, 8, false, PROB>(a, grid_override, s)
-                : run_batched<double, 4, false, PROB>(a, grid_override, s);
+    return wide ? run_batched<double, 8, false, PROB>(a, n_cells, grid_override, s)
+                : run_batched<double, 4, false, PROB>(a, n_cells, grid_override, s);
   if (fast)
-    return wide ? run_batched<float, 8, true, PROB>(a, grid_override, s)
-                : run_batched<float, 4, true, PROB>(a, grid_override, s);
-  return wide ? run_batched<float, 8, false, PROB>(a, grid_override, s)
-              : run_batched<float, 4, false, PROB>(a, grid_override, s);
+    return wide ? run_batched<float, 8, true, PROB>(a, n_cells, grid_override, s)
+                : run_batched<float, 4, true, PROB>(a, n_cells, grid_override, s);
+  return wide ? run_batched<float, 8, false, PROB>(a, n_cells, grid_override, s)
+              : run_batched<float, 4, false, PROB>(a, n_cells, grid_override, s);
 }
 
 template <bool PROB>
