@@ -107,11 +107,23 @@ struct DiskPoint {
   double Sigma_g, T, cs, Omega, H, rho_g;
 };
 
+// x^-e: the half-integer exponents of disk models (1/2, 1, 3/2) by roots and
+// products, within an ulp like pow, whose 300 FP64 instructions set the pace of
+// a kernel over all particles.  (The cells' gas keeps pow: an ulp there could
+// round a cell's FP32 constants the other way.)
+__host__ __device__ inline double inverse_power(double x, double e) {
+  if (e == 1.0) return 1.0 / x;
+  if (e == 0.5) return 1.0 / sqrt(x);
+  if (e == 1.5) return 1.0 / (x * sqrt(x));
+  return pow(x, -e);
+}
+
+template <bool ROOTS = false>
 __host__ __device__ inline DiskPoint disk_at(const Model &P, double r, double z) {
   DiskPoint d;
   const double x = r / P.r_ref;
-  d.Sigma_g = P.sigma_g0 * pow(x, -P.p);
-  d.T = P.T0 * pow(x, -P.q);
+  d.Sigma_g = P.sigma_g0 * (ROOTS ? inverse_power(x, P.p) : pow(x, -P.p));
+  d.T = P.T0 * (ROOTS ? inverse_power(x, P.q) : pow(x, -P.q));
   d.cs = sqrt(kBoltz * d.T / (P.mu * kMassH));
   d.Omega = sqrt(kGrav * P.m_star / (r * r * r));
   d.H = d.cs / d.Omega;
@@ -158,11 +170,12 @@ __host__ __device__ inline void grid_locate(const double *nodes, int n, double x
 // power-law disk, or the gridded gas: bilinear in (ln r, z) of ln rho_g,
 // ln T and ln alpha, with the r-slopes of those interpolants at this height;
 // the surface density's slope from its radial nodes
+template <bool ROOTS = false>
 __host__ __device__ inline LocalGas local_gas_at(const Model &P, double r, double z) {
   LocalGas o;
   const GasGridView &G = P.grid;
   if (G.nr == 0) {
-    const DiskPoint d = disk_at(P, r, z);
+    const DiskPoint d = disk_at<ROOTS>(P, r, z);
     o.rho_g = d.rho_g;
     o.T = d.T;
     o.cs = d.cs;
