@@ -57,7 +57,9 @@ inline hipError_t run_batched(const CollideArgs &a, int n_cells, int grid_overri
   // workgroups, 73 with 768)
   int grid = std::min(per_cu * cus, std::max(n_cells, 1));
   if (grid_override > 0) grid = grid_override;
-  kern<<<grid, 256, lds, s>>>(a);
+  CollideArgs b = a;
+  b.seeded = grid <= per_cu * cus ? 1 : 0;
+  kern<<<grid, 256, lds, s>>>(b);
   return hipGetLastError();
 }
 
