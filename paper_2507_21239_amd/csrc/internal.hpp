@@ -68,7 +68,7 @@ struct CollideArgs {
   int32_t *evlog;
   int64_t log_per_cell;
   double *rowsum_dump;  // test path: starting row sums written here, no events
-  int32_t seeded = 0;       // every workgroup of the batched launch is resident from the start
+  int32_t seeded = 0;   // every workgroup of the batched launch is resident from the start
 };
 
 // a published selection of a four-wave team: mass of the chosen particle, the
