@@ -240,11 +240,13 @@ __global__ __launch_bounds__(256) void k_radix_scan_rows(uint32_t *hist, int til
 // range, so consecutive lanes write consecutive words.  Bound by the passes
 // over keys and indices and the launch: at 1e6 particles 9.5 us a pass of 32-bit
 // keys, 13.5 with the items of all four waves in turn and five barriers each.
-template <typename KeyT>
+// TWICE: the indices go to vcopy as well.
+template <typename KeyT, bool TWICE>
 __global__ __launch_bounds__(256) void k_radix_scatter(const KeyT *__restrict__ kin,
                                                        const int32_t *__restrict__ vin,
                                                        KeyT *__restrict__ kout,
-                                                       int32_t *__restrict__ vout, int64_t N,
+                                                       int32_t *__restrict__ vout,
+                                                       int32_t *__restrict__ vcopy, int64_t N,
                                                        int shift, const uint32_t *hist,
                                                        const uint32_t *digit_tot, int tiles) {
   __shared__ KeyT sk[kRadixTile];
@@ -325,21 +327,23 @@ __global__ __launch_bounds__(256) void k_radix_scatter(const KeyT *__restrict__ 
       const uint32_t g = gofs[(uint32_t)(k >> shift) & 255u] + (uint32_t)p;
       kout[g] = k;
       vout[g] = sv[p];
+      if (TWICE) vcopy[g] = sv[p];
     }
   }
 }
 
-// have_hist: the tile histograms of this pass are already in hist
+// have_hist: the tile histograms of this pass are already in hist; vcopy: where
+// a second copy of the indices goes, or nullptr
 template <typename KeyT>
 static hipError_t radix_pass(KeyT *const keys[2], int32_t *const vals[2], uint32_t *hist,
                              uint32_t *digit_tot, int &cur, int64_t N, int shift, hipStream_t s,
-                             bool have_hist = false) {
+                             bool have_hist = false, int32_t *vcopy = nullptr) {
   const int tiles = radix_tiles(N);
   if (!have_hist) k_radix_hist<KeyT><<<tiles, kRadixThreads, 0, s>>>(keys[cur], N, shift, hist, tiles);
   k_radix_scan_rows<<<256, 256, 0, s>>>(hist, tiles, digit_tot);
-  k_radix_scatter<KeyT><<<tiles, kRadixThreads, 0, s>>>(keys[cur], vals[cur], keys[cur ^ 1],
-                                                        vals[cur ^ 1], N, shift, hist, digit_tot,
-                                                        tiles);
+  auto scatter = vcopy ? k_radix_scatter<KeyT, true> : k_radix_scatter<KeyT, false>;
+  scatter<<<tiles, kRadixThreads, 0, s>>>(keys[cur], vals[cur], keys[cur ^ 1], vals[cur ^ 1], vcopy,
+                                          N, shift, hist, digit_tot, tiles);
   cur ^= 1;
   return hipGetLastError();
 }
@@ -347,37 +351,26 @@ static hipError_t radix_pass(KeyT *const keys[2], int32_t *const vals[2], uint32
 // ---------------------------------------------------------------------------
 // exact order inside runs of equal 32-bit keys: by full r bits, then index.
 // Stability leaves every run in index order, so a run needs work only if two
-// neighbours in it differ in r.  The first kernel copies the order out and
-// flags such neighbours; the second lets the first flagged position of each
-// run (flags and keys are read-only there) insertion-sort the run by
-// (bits of r, index).
+// neighbours in it differ in r.  The first such position of each run
+// insertion-sorts the run in by_r, a copy of the order, by (bits of r, index);
+// keys and vals are read-only here.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_ties_copy(const uint32_t *__restrict__ keys,
-                                                   const int32_t *__restrict__ vals,
-                                                   const double *__restrict__ r, int64_t N,
-                                                   const DevState *st, int32_t *__restrict__ by_r,
-                                                   uint8_t *__restrict__ flag) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= N) return;
-  const int32_t v = vals[p];
-  by_r[p] = v;
-  uint8_t f = 0;
-  if (p + 1 < (int64_t)st->n_active && keys[p + 1] == keys[p])
-    f = key_bits(r[v]) != key_bits(r[vals[p + 1]]) ? 1 : 0;
-  flag[p] = f;
-}
-
 __global__ __launch_bounds__(256) void k_fix_ties(const uint32_t *__restrict__ keys,
-                                                  const uint8_t *__restrict__ flag,
-                                                  const double *__restrict__ r, int64_t N,
-                                                  const DevState *st, int32_t *by_r) {
+                                                  const int32_t *__restrict__ vals,
+                                                  const double *__restrict__ r, const DevState *st,
+                                                  int32_t *by_r) {
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= N || !flag[p]) return;
   const int64_t na = st->n_active;
+  if (p + 1 >= na) return;
   const uint32_t k = keys[p];
+  if (keys[p + 1] != k) return;
+  auto differs = [&](int64_t a) {  // from its successor, of the same key
+    return key_bits(r[vals[a]]) != key_bits(r[vals[a + 1]]);
+  };
+  if (!differs(p)) return;
   int64_t s = p;
   while (s > 0 && keys[s - 1] == k) {
-    if (flag[s - 1]) return;  // an earlier position of this run does the work
+    if (differs(s - 1)) return;  // an earlier position of this run does the work
     --s;
   }
   int64_t e = p + 2;
@@ -857,11 +850,10 @@ hipError_t launch_binning(const Model &P, int n_r, int n_z, const double *r, con
                                                   b.k32[0], b.vals[0], b.hist, tiles);
   int cur = 0;
   for (int sh = 0; sh < 32; sh += 8)
-    if ((e = radix_pass<uint32_t>(b.k32, b.vals, b.hist, b.digit_tot, cur, N, sh, s, sh == 0)) !=
-        hipSuccess)
+    if ((e = radix_pass<uint32_t>(b.k32, b.vals, b.hist, b.digit_tot, cur, N, sh, s, sh == 0,
+                                  sh == 24 ? b.by_r : nullptr)) != hipSuccess)
       return e;
-  k_ties_copy<<<g1, 256, 0, s>>>(b.k32[cur], b.vals[cur], r, N, state, b.by_r, b.flag);
-  k_fix_ties<<<g1, 256, 0, s>>>(b.k32[cur], b.flag, r, N, state, b.by_r);
+  k_fix_ties<<<g1, 256, 0, s>>>(b.k32[cur], b.vals[cur], r, state, b.by_r);
   // 2. rank by (z, index) inside each zone
   const int64_t zone_max = (N + n_r - 1) / n_r;  // no zone holds more
   if (zone_max > kZoneSortMax && (b.keys[0] == nullptr || b.zone == nullptr))

@@ -31,7 +31,7 @@ struct Layout {
   size_t big, small, hist, cursor;            // cell lists and their planning
   size_t mbak, cbak;                          // tuning backups of m and comp
   size_t edges;                               // histogram edges
-  size_t k32[2], vals[2], flag, part, by_r, hist_r, digit, k64[2], zone;  // binning
+  size_t k32[2], vals[2], part, by_r, hist_r, digit, k64[2], zone;  // binning
   size_t total;
   int64_t cells_adaptive, cells_cap;
   int tiles;
@@ -69,7 +69,6 @@ Layout layout_for(const mcd_params &p, int64_t N) {
     L.k32[k] = take(n * sizeof(uint32_t));
     L.vals[k] = take(n * sizeof(int32_t));
   }
-  L.flag = take(n);
   L.part = take((size_t)3 * kMinmaxParts * sizeof(uint64_t));
   L.by_r = take(n * sizeof(int32_t));
   L.hist_r = take((size_t)256 * L.tiles * sizeof(uint32_t));
@@ -274,7 +273,6 @@ void carve(mcd_ctx *c) {
     b.vals[k] = (int32_t *)(w + L.vals[k]);
     b.keys[k] = L.global_z ? (uint64_t *)(w + L.k64[k]) : nullptr;
   }
-  b.flag = (uint8_t *)(w + L.flag);
   b.part = (uint64_t *)(w + L.part);
   b.by_r = (int32_t *)(w + L.by_r);
   b.zone = L.global_z ? (int32_t *)(w + L.zone) : nullptr;
@@ -798,7 +796,7 @@ mcd_status mcd_sigma_hist(mcd_ctx *c, const double *r_edges, int32_t n_rb, const
   // scratch: the radix sort's keys and values, which no binning reads before writing them
   hipError_t e = launch_sigma_hist(c->part.r, c->part.m, c->part.M, c->part.active, c->part.n, re,
                                    n_rb, me, n_mb, c->prm.column ? 1 : 0, sigma, count, c->cus,
-                                   c->ws + c->L.k32[0], c->L.flag - c->L.k32[0], c->stream);
+                                   c->ws + c->L.k32[0], c->L.part - c->L.k32[0], c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "sigma_hist");
   return MCD_OK;
 }

@@ -218,7 +218,6 @@ struct BinBuffers {
   uint64_t *keys[2];   // 64-bit keys of the global z path
   uint32_t *k32[2];    // 32-bit keys of the r sort
   int32_t *vals[2];
-  uint8_t *flag;       // neighbours with equal r keys but different r
   uint64_t *part;      // [3 kMinmaxParts] partial {min, max, count}
   int32_t *by_r;       // active particle indices by ascending (r, index)
   int32_t *zone;       // zone of every particle (n_r for inactive)
