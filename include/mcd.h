@@ -307,8 +307,9 @@ mcd_status mcd_set_gas_grid(mcd_ctx *ctx, const double *r_nodes, int32_t n_gr,
  * pi (r_edges[k+1]^2 - r_edges[k]^2) (area 1 in column mode, where M is per
  * unit area): g/cm^2 per mass bin.  count [n_rb*n_mb]: device uint32, the
  * representative particles per bin, or NULL.  The edges go to the
- * workspace (at most 2^16 in all); the call synchronises the stream first
- * (no earlier upload still reads the host copy), then runs async.
+ * workspace (at most 2^16 in all); above 448 edges the call synchronises the
+ * stream first (no earlier upload still reads the host copy); then it runs
+ * async.
  * The FP64 sums follow the order of device atomics (results may differ by
  * a relative count * 2^-52 between runs).  MCD_EINVAL on bad edges or
  * n_rb * n_mb outside [1, 2^24]. */

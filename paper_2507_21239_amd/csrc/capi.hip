@@ -786,12 +786,26 @@ mcd_status mcd_sigma_hist(mcd_ctx *c, const double *r_edges, int32_t n_rb, const
   const size_t ne = (size_t)n_rb + 1 + (size_t)n_mb + 1;
   if ((int64_t)ne > kMaxEdges)
     return fail(c, MCD_EINVAL, "at most " + std::to_string(kMaxEdges) + " bin edges in all");
-  // the previous histogram's upload must be done before its host copy is replaced
-  MCD_HIP(c, hipStreamSynchronize(c->stream));
-  c->h_edges.assign(r_edges, r_edges + n_rb + 1);
-  c->h_edges.insert(c->h_edges.end(), m_edges, m_edges + n_mb + 1);
-  MCD_HIP(c, hipMemcpyAsync(c->d_edges, c->h_edges.data(), ne * sizeof(double),
-                            hipMemcpyHostToDevice, c->stream));
+  if (ne <= kArgEdges) {
+    // few edges travel with a launch: no synchronisation and no copy from
+    // pageable memory (a histogram of 2e6 particles: 21.7 against 34 us).  A
+    // capturing stream is refused, as where the call synchronises
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    MCD_HIP(c, hipStreamIsCapturing(c->stream, &cap));
+    if (cap != hipStreamCaptureStatusNone)
+      return hip_fail(c, hipErrorStreamCaptureUnsupported, "sigma_hist");
+    double h[kArgEdges];
+    std::copy(r_edges, r_edges + n_rb + 1, h);
+    std::copy(m_edges, m_edges + n_mb + 1, h + n_rb + 1);
+    MCD_HIP(c, launch_put_edges(h, (int)ne, c->d_edges, c->stream));
+  } else {
+    // the previous histogram's upload must be done before its host copy is replaced
+    MCD_HIP(c, hipStreamSynchronize(c->stream));
+    c->h_edges.assign(r_edges, r_edges + n_rb + 1);
+    c->h_edges.insert(c->h_edges.end(), m_edges, m_edges + n_mb + 1);
+    MCD_HIP(c, hipMemcpyAsync(c->d_edges, c->h_edges.data(), ne * sizeof(double),
+                              hipMemcpyHostToDevice, c->stream));
+  }
   const double *re = c->d_edges, *me = c->d_edges + n_rb + 1;
   // scratch: the radix sort's keys and values, which no binning reads before writing them
   hipError_t e = launch_sigma_hist(c->part.r, c->part.m, c->part.M, c->part.active, c->part.n, re,

@@ -66,9 +66,9 @@ __global__ __launch_bounds__(256) void k_hist_clear(double *sigma, uint32_t *cou
 // Workgroup (w, p) takes the particles [w chunk, (w+1) chunk) and the bins of
 // `rows` radial rows from p rows on; its sums and counts go to row w of the
 // scratch.  Bound by the one pass over the particles: at 2e6 particles in no
-// radial order and 60 x 90 bins the call takes 34 us (10 us at the rate of a
-// large copy, 20 us on the host, beside which the kernels run), by atomics on
-// global memory, two a particle, 236 us.
+// radial order and 60 x 90 bins the call takes 21.7 us (10 us at the rate of a
+// large copy; this launch 15, the next 7), by atomics on global memory, two a
+// particle, 236 us.
 __global__ __launch_bounds__(kHistThreads) void k_hist_lds(
     const double *__restrict__ r, const double *__restrict__ m, const double *__restrict__ M,
     const uint8_t *__restrict__ active, int64_t N, int64_t chunk, const double *__restrict__ re,
@@ -163,9 +163,17 @@ __global__ __launch_bounds__(256) void k_hist_global(const double *__restrict__ 
                                                      const double *__restrict__ m,
                                                      const double *__restrict__ M,
                                                      const uint8_t *__restrict__ active, int64_t N,
-                                                     const double *__restrict__ re, int n_rb,
-                                                     const double *__restrict__ me, int n_mb,
+                                                     const double *re, int n_rb,
+                                                     const double *me, int n_mb,
                                                      double *sigma, uint32_t *count) {
+  __shared__ double le[kHistLdsEdges];
+  if (n_rb + n_mb + 2 <= kHistLdsEdges) {
+    for (int k = threadIdx.x; k <= n_rb; k += blockDim.x) le[k] = re[k];
+    for (int k = threadIdx.x; k <= n_mb; k += blockDim.x) le[n_rb + 1 + k] = me[k];
+    __syncthreads();
+    re = le;
+    me = le + n_rb + 1;
+  }
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N;
        i += (int64_t)gridDim.x * blockDim.x) {
     if (!active[i]) continue;
@@ -185,6 +193,19 @@ __global__ __launch_bounds__(256) void k_hist_area(double *sigma, const double *
   sigma[b] /= bin_area(re, (int)(b / n_mb), column);
 }
 
+// one edge a thread, from the launch's arguments
+__global__ __launch_bounds__(kArgEdges) void k_put_edges(EdgeArgs a, int n, double *dst) {
+  const int k = threadIdx.x;
+  if (k < n) dst[k] = a.e[k];
+}
+
+hipError_t launch_put_edges(const double *host, int n, double *dst, hipStream_t s) {
+  EdgeArgs a{};
+  for (int k = 0; k < n; ++k) a.e[k] = host[k];
+  k_put_edges<<<1, kArgEdges, 0, s>>>(a, n, dst);
+  return hipGetLastError();
+}
+
 hipError_t launch_sigma_hist(const double *r, const double *m, const double *M,
                              const uint8_t *active, int64_t N, const double *re, int n_rb,
                              const double *me, int n_mb, int column, double *sigma,
@@ -197,8 +218,8 @@ hipError_t launch_sigma_hist(const double *r, const double *m, const double *M,
   // workgroups: one per CU, each with a full round of particles and a row of
   // scratch.  Below 5 particles a bin clearing and adding up the rows takes
   // longer than the atomics (120 x 140 bins: at 4.5e4 particles 31.6 against
-  // 27.0 us with the call's 20 us on the host, at 8e4 30.5 against 30.7; 60 x 90
-  // bins, 3e4: 23.0 against 25.7; 2e6: 34 against 236)
+  // 27.0 us, at 8e4 30.5 against 30.7; 60 x 90 bins, 3e4: 23.0 against 25.7; all
+  // with 12 us of host work that the call no longer has)
   int64_t gw = std::min<int64_t>(std::max(1, cus / parts), (N + kHistThreads - 1) / kHistThreads);
   gw = std::min<int64_t>(gw, (int64_t)(scratch_bytes / ((size_t)nb * 12)));
   if (N >= 5 * nb && gw >= 1 && parts <= kHistParts && ne <= kHistLdsEdges) {

@@ -226,6 +226,13 @@ struct BinBuffers {
   int64_t cap;         // particles
   int32_t tiles;
 };
+// bin edges that travel with a launch; more go through the workspace
+constexpr int kArgEdges = 448;
+struct EdgeArgs {
+  double e[kArgEdges];
+};
+// writes n <= kArgEdges edges to device memory (diagnostics.hip)
+hipError_t launch_put_edges(const double *host, int n, double *dst, hipStream_t s);
 // sigma_d(m, r) histogram of the particles (diagnostics.hip)
 hipError_t launch_sigma_hist(const double *r, const double *m, const double *M,
                              const uint8_t *active, int64_t N, const double *re, int n_rb,
