@@ -962,7 +962,10 @@ __device__ __forceinline__ void run_events(const CollideArgs &A, const PairConst
       fast = !(cj.x < (RT)oc_par.v_frag);
     }
     if (null) {
-      cj.m = 0.0;
+      // a partner of i's own mass: nothing takes the outcome, but it has to be
+      // a valid mass (of zero mass, the FP64 grouping factor would be infinite
+      // and the outcome not a number)
+      cj.m = mi;
       fast = false;
       ++n_null;
     }
