@@ -212,12 +212,15 @@ __global__ __launch_bounds__(1024) void k_plan_small(const int32_t *__restrict__
     if (size > small_max) atomicAdd(&s_big, 1u);
   }
   __syncthreads();
-  if (!s_bad) {  // as the sizes hold, cn - c0 <= nc * bound
+  if (!s_bad) {  // as the sizes hold, cn - c0 <= nc * bound; counted from c0,
+                 // as the rounded-up end may pass 2^31
     bool bad = false;
-    for (int32_t k = c0 + t; k < cn; k += 8 * 1024) {
+    const int32_t *const mem = order + c0;
+    const int32_t len = cn - c0;
+    for (int32_t k = t; k < len; k += 8 * 1024) {
       int32_t p[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) p[e] = order[min(k + e * 1024, cn - 1)];
+      for (int e = 0; e < 8; ++e) p[e] = mem[min(k + e * 1024, len - 1)];
 #pragma unroll
       for (int e = 0; e < 8; ++e) bad |= p[e] < 0 || (int64_t)p[e] >= N;
     }
