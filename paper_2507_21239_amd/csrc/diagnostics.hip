@@ -22,6 +22,9 @@ constexpr int kHistThreads = 1024;  // one workgroup per CU
 constexpr int kHistLdsBins = 12800;  // 12 bytes each; with the edges within the 160 KB of LDS
 constexpr int kHistLdsEdges = 1024;
 constexpr int kHistParts = 4;
+constexpr int kHistFewBins = 4096;  // in LDS for any number of particles and edges
+static_assert(kHistLdsEdges * 8 + kHistLdsBins * 12 <= 160 * 1024, "one part fits");
+static_assert((kHistFewBins + 3) * 8 + kHistFewBins * 12 <= 160 * 1024, "few bins in any shape fit");
 constexpr int kHistUnroll = 4;
 
 // bin of x by binary search: e[k] <= x < e[k+1], -1 outside the edges
@@ -65,10 +68,11 @@ __global__ __launch_bounds__(256) void k_hist_clear(double *sigma, uint32_t *cou
 
 // Workgroup (w, p) takes the particles [w chunk, (w+1) chunk) and the bins of
 // `rows` radial rows from p rows on; its sums and counts go to row w of the
-// scratch.  Bound by the one pass over the particles: at 2e6 particles in no
-// radial order and 60 x 90 bins the call takes 21.7 us (10 us at the rate of a
-// large copy; this launch 15, the next 7), by atomics on global memory, two a
-// particle, 236 us.
+// scratch (a lone workgroup's to the outputs, where counts may be unwanted).
+// Bound by the one pass over the particles: at 2e6 particles in no radial order
+// and 60 x 90 bins the call takes 21.7 us (10 us at the rate of a large copy;
+// this launch 15, the next 7), by atomics on global memory, two a particle,
+// 236 us.
 __global__ __launch_bounds__(kHistThreads) void k_hist_lds(
     const double *__restrict__ r, const double *__restrict__ m, const double *__restrict__ M,
     const uint8_t *__restrict__ active, int64_t N, int64_t chunk, const double *__restrict__ re,
@@ -115,7 +119,7 @@ __global__ __launch_bounds__(kHistThreads) void k_hist_lds(
   const int64_t row = (int64_t)blockIdx.x * n_rb * n_mb + (int64_t)k0 * n_mb;
   for (int b = threadIdx.x; b < nb; b += kHistThreads) {
     psum[row + b] = ls[b];
-    pcount[row + b] = lc[b];
+    if (pcount) pcount[row + b] = lc[b];
   }
 }
 
@@ -219,10 +223,16 @@ hipError_t launch_sigma_hist(const double *r, const double *m, const double *M,
   // scratch.  Below 5 particles a bin clearing and adding up the rows takes
   // longer than the atomics (120 x 140 bins: at 4.5e4 particles 31.6 against
   // 27.0 us, at 8e4 30.5 against 30.7; 60 x 90 bins, 3e4: 23.0 against 25.7; all
-  // with 12 us of host work that the call no longer has)
+  // with 12 us of host work that the call no longer has).  Few bins are in LDS
+  // for any number of particles and edges: 16 against 19 us, and where the
+  // particles share bins, whose atomics wait for one another, 17 against 275
+  // (20479 in one of 64 x 64 bins)
   int64_t gw = std::min<int64_t>(std::max(1, cus / parts), (N + kHistThreads - 1) / kHistThreads);
   gw = std::min<int64_t>(gw, (int64_t)(scratch_bytes / ((size_t)nb * 12)));
-  if (N >= 5 * nb && gw >= 1 && parts <= kHistParts && ne <= kHistLdsEdges) {
+  const bool few = nb <= kHistFewBins;
+  if (few || (N >= 5 * nb && gw >= 1 && parts <= kHistParts && ne <= kHistLdsEdges)) {
+    const bool alone = gw < 1;  // too few particles for a row of scratch: one workgroup
+    gw = std::max<int64_t>(gw, 1);
     const int64_t chunk = (N + gw - 1) / gw;
     const size_t lds = (size_t)ne * 8 + (size_t)rows * n_mb * 12;
     hipError_t e = hipSuccess;
@@ -230,10 +240,14 @@ hipError_t launch_sigma_hist(const double *r, const double *m, const double *M,
       e = hipFuncSetAttribute((const void *)k_hist_lds, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)lds);
     if (e != hipSuccess) return e;
-    double *psum = (double *)scratch;
-    uint32_t *pcount = (uint32_t *)(psum + gw * nb);
+    double *psum = alone ? sigma : (double *)scratch;
+    uint32_t *pcount = alone ? count : (uint32_t *)(psum + gw * nb);
     k_hist_lds<<<dim3((unsigned)gw, (unsigned)parts), kHistThreads, lds, s>>>(
         r, m, M, active, N, chunk, re, n_rb, me, n_mb, rows, psum, pcount);
+    if (alone) {
+      k_hist_area<<<(unsigned)((nb + 255) / 256), 256, 0, s>>>(sigma, re, n_rb, n_mb, column);
+      return hipGetLastError();
+    }
     k_hist_reduce<<<(unsigned)((nb + 31) / 32), 1024, 0, s>>>(psum, pcount, (int)gw, re, n_rb, n_mb,
                                                               column, sigma, count);
     return hipGetLastError();
