@@ -163,11 +163,15 @@ __global__ __launch_bounds__(1024) void k_hist_reduce(const double *__restrict__
   }
 }
 
+// Every particle adds to global memory; bound by the rate of the atomics.  A
+// workgroup takes a contiguous range, so that in particles stored by radius the
+// workgroups at work at one time fall on different bins (2e6 of them in 2000 x 4
+// bins: 151 us, in strides over the whole grid 239).
 __global__ __launch_bounds__(256) void k_hist_global(const double *__restrict__ r,
                                                      const double *__restrict__ m,
                                                      const double *__restrict__ M,
                                                      const uint8_t *__restrict__ active, int64_t N,
-                                                     const double *re, int n_rb,
+                                                     int64_t chunk, const double *re, int n_rb,
                                                      const double *me, int n_mb,
                                                      double *sigma, uint32_t *count) {
   __shared__ double le[kHistLdsEdges];
@@ -178,8 +182,9 @@ __global__ __launch_bounds__(256) void k_hist_global(const double *__restrict__ 
     re = le;
     me = le + n_rb + 1;
   }
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N;
-       i += (int64_t)gridDim.x * blockDim.x) {
+  const int64_t i0 = (int64_t)blockIdx.x * chunk;
+  const int64_t i1 = i0 + chunk < N ? i0 + chunk : N;
+  for (int64_t i = i0 + threadIdx.x; i < i1; i += blockDim.x) {
     if (!active[i]) continue;
     const int k = find_bin(re, n_rb, r[i]);
     const int l = find_bin(me, n_mb, m[i]);
@@ -255,7 +260,9 @@ hipError_t launch_sigma_hist(const double *r, const double *m, const double *M,
   const unsigned gb = (unsigned)std::min<int64_t>((nb + 255) / 256, 4096);
   k_hist_clear<<<gb, 256, 0, s>>>(sigma, count, nb);
   const int64_t gp = std::max<int64_t>(1, std::min<int64_t>((N + 255) / 256, 4 * (int64_t)cus));
-  k_hist_global<<<(unsigned)gp, 256, 0, s>>>(r, m, M, active, N, re, n_rb, me, n_mb, sigma, count);
+  const int64_t chunk = (N + gp - 1) / gp;
+  k_hist_global<<<(unsigned)gp, 256, 0, s>>>(r, m, M, active, N, chunk, re, n_rb, me, n_mb, sigma,
+                                             count);
   k_hist_area<<<(unsigned)((nb + 255) / 256), 256, 0, s>>>(sigma, re, n_rb, n_mb, column);
   return hipGetLastError();
 }
