@@ -1,12 +1,13 @@
 """Compile the HIP sources into paper_2507_21239_amd/libmcd.so for gfx950.
 
 hipcc cross-compiles without a GPU.  Flags: -O3, no FP contraction (the FP64
-path keeps the operation order of its formulas; FP32 code asks for fused
-multiply-adds explicitly where it wants them), packed FP32 instructions
-disabled.  collide_ilp.hip and collide_ilp3.hip (the batched kernels of the
-mixed form's common path) are also scheduled for instruction-level parallelism;
-the other collision kernels and collide_ilp3.hip sink instructions into the
-loops where they are used rather than spill their results.
+path keeps the operations of its formulas as they are written; FP32 code asks
+for fused multiply-adds explicitly where it wants them), packed FP32
+instructions disabled.  collide_ilp.hip and collide_ilp3.hip (the batched
+kernels of the mixed form's common path) are also scheduled for
+instruction-level parallelism; the other collision kernels, but for
+collide_fp64_timed.hip, and collide_ilp3.hip sink instructions into the loops
+where they are used rather than spill their results.
 """
 from __future__ import annotations
 
@@ -20,9 +21,10 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libmcd.so")
-SOURCES = ["collide_batched.hip", "collide_batched_prob.hip", "collide_fp64.hip", "collide_ilp.hip",
-           "collide_ilp3.hip", "collide_plain.hip", "collide_plain_prob.hip", "capi.hip", "collide.hip",
-           "binning.hip", "plan.hip", "transport.hip", "diagnostics.hip", "noalloc.hip"]
+SOURCES = ["collide_batched.hip", "collide_batched_prob.hip", "collide_fp64.hip",
+           "collide_fp64_timed.hip", "collide_ilp.hip", "collide_ilp3.hip", "collide_plain.hip",
+           "collide_plain_prob.hip", "capi.hip", "collide.hip", "binning.hip", "plan.hip",
+           "transport.hip", "diagnostics.hip", "noalloc.hip"]
 # per-file flags on top of CFLAGS
 ILP = ["-mllvm", "--amdgpu-sched-strategy=max-ilp"]
 SINK = ["-mllvm", "-sink-insts-to-avoid-spills=1"]

@@ -154,10 +154,13 @@ __device__ inline void build_pair(const PairConst<double> &c, const Rec<double> 
 // lane X is always held by the lane currently paired with X; after step 32 it
 // sits at lane X - 32 and returns with one exchange of the wave's halves.
 // Sums are in the rate precision, in an order that differs from the members';
-// slots past the cell's particles get 0.
+// slots past the cell's particles get 0.  In FP64, where a step takes longest, a
+// cell of at most 32 lanes ends after the step of its last pair of lanes (the
+// further steps add zeros).
 template <typename RT, int KMAX>
 __device__ inline void build_rows_pairwise(const RecStore<RT> &R, const PairConst<RT> &pc,
                                            int K, int lane, int n, double r[KMAX]) {
+  const int steps = sizeof(RT) == 8 ? min(32, (n + K - 1) / K - 1) : 32;
   Rec<RT> mine[KMAX];
   RT acc[KMAX], pacc[KMAX];
 #pragma unroll
@@ -179,7 +182,7 @@ __device__ inline void build_rows_pairwise(const RecStore<RT> &R, const PairCons
     }
   }
 #pragma unroll 1
-  for (int d = 1; d <= 32; ++d) {
+  for (int d = 1; d <= steps; ++d) {
     const int c = (lane + d) & 63;
     Rec<RT> pr[KMAX];
 #pragma unroll
@@ -198,7 +201,7 @@ __device__ inline void build_rows_pairwise(const RecStore<RT> &R, const PairCons
         }
       }
     }
-    if (d < 32) {
+    if (d < steps) {
 #pragma unroll
       for (int J = 0; J < KMAX; ++J)  // lane l takes lane l + 1's accumulators
         pacc[J] = dpp_t<0x134, 0xf, 0xf>(pacc[J]);
@@ -206,7 +209,8 @@ __device__ inline void build_rows_pairwise(const RecStore<RT> &R, const PairCons
   }
 #pragma unroll
   for (int q = 0; q < KMAX; ++q) {
-    const RT home = __shfl_xor(pacc[q], 32, 64);
+    const RT home = sizeof(RT) == 8 ? __shfl(pacc[q], (lane - steps) & 63, 64)
+                                    : __shfl_xor(pacc[q], 32, 64);
     r[q] = (q < K && lane * K + q < n) ? (double)(acc[q] + home) : 0.0;
   }
 }
@@ -225,6 +229,7 @@ __device__ inline void build_rows_pairwise_team(const RecStore<RT> &R, const Pai
   static_assert(KMAX % 2 == 0, "partner sums go over in pairs of slots");
   constexpr int TL = 256;
   const int own = wave * 64;
+  const bool mine_any = own * K < n;
   Rec<RT> mine[KMAX];
   RT acc[KMAX], pacc[KMAX];
 #pragma unroll
@@ -282,8 +287,11 @@ __device__ inline void build_rows_pairwise_team(const RecStore<RT> &R, const Pai
   for (int p = 1; p <= 3; ++p) {
     const int b = (wave + p) & 3;
     const int d0 = wave < b ? 0 : 1;
+    // (FP64, where a step takes longest: none against or of an empty wave, which
+    // would add zeros)
+    const int n_st = sizeof(RT) == 4 || (mine_any && b * 64 * K < n) ? 32 : 0;
 #pragma unroll 1
-    for (int st = 0; st < 32; ++st) {
+    for (int st = 0; st < n_st; ++st) {
       const int c = (lane + d0 + st) & 63;
       Rec<RT> pr[KMAX];
 #pragma unroll
@@ -324,6 +332,25 @@ __device__ inline void build_rows_pairwise_team(const RecStore<RT> &R, const Pai
   const int tl = own + lane;
 #pragma unroll
   for (int q = 0; q < KMAX; ++q) r[q] = (q < K && tl * K + q < n) ? (double)acc[q] : 0.0;
+}
+
+// Four-wave teams with one slot per lane at most: every row over the n members in
+// their order.  The 128 steps of the scheme above take as long as 192 members
+// here (FP64, physical kernel: one cell of 64 / 192 / 256 particles 36 / 96 / 113
+// us against 97, 3000 cells of 128 / 192 / 256 494 / 758 / 1031 against 641)
+constexpr int kPlainRows = 192;
+template <typename RT, int KMAX>
+__device__ inline void build_rows_plain(const RecStore<RT> &R, const PairConst<RT> &pc, int tl,
+                                        int n, double r[KMAX]) {
+  const Rec<RT> mine = R.load(tl);
+  RT acc = (RT)0;
+  for (int k = 0; k < n; ++k) {
+    RT dv, rxy, ryx;
+    PairEval<RT, false>::run(pc, mine, R.load(k), dv, rxy, ryx);
+    acc += rxy;
+  }
+#pragma unroll
+  for (int q = 0; q < KMAX; ++q) r[q] = q == 0 && tl < n ? (double)acc : 0.0;
 }
 
 // ---------------------------------------------------------------------------
@@ -1154,11 +1181,14 @@ __device__ __forceinline__ void process_cell(const CollideArgs &A, int cell, cha
   double r[KMAX];
   bool built = false;
   if constexpr ((sizeof(RT) == 8 || FAST) && KMAX == 4) {
-    if (nw == 1)
+    if (nw == 1) {
       build_rows_pairwise<RT, KMAX>(R, pc, K, lane, n, r);
-    else
+    } else if (sizeof(RT) == 8 && n <= kPlainRows) {
+      build_rows_plain<RT, KMAX>(R, pc, tl, n, r);
+    } else {
       build_rows_pairwise_team<RT, KMAX>(R, pc, K, wave, lane, n,
                                          (Pair2<RT> *)(base + xbuf_offset<RT>(cap)), r);
+    }
     built = true;
   }
   if (!built) {

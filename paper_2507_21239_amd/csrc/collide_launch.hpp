@@ -8,12 +8,15 @@
 
 namespace mcd {
 
-// defined in collide_ilp.hip, collide_ilp3.hip and collide_fp64.hip
+// defined in collide_ilp.hip, collide_ilp3.hip, collide_fp64.hip and
+// collide_fp64_timed.hip
 extern template __global__ void collide_batched<float, 4, true, false, false, kTimeLimited>(
     CollideArgs A);
 extern template __global__ void collide_batched<float, 4, true, false, true, kTimeLimited>(
     CollideArgs A);
 extern template __global__ void collide_batched<float, 4, true, false, false, kFixedCount>(
+    CollideArgs A);
+extern template __global__ void collide_batched<double, 4, false, false, false, kEitherLimit>(
     CollideArgs A);
 extern template __global__ void collide_batched<double, 4, false, false, false, kFixedCount>(
     CollideArgs A);
