@@ -5,9 +5,10 @@ path keeps the operations of its formulas as they are written; FP32 code asks
 for fused multiply-adds explicitly where it wants them), packed FP32
 instructions disabled.  collide_ilp.hip and collide_ilp3.hip (the batched
 kernels of the mixed form's common path) are also scheduled for
-instruction-level parallelism; the other collision kernels, but for
-collide_fp64_timed.hip, and collide_ilp3.hip sink instructions into the loops
-where they are used rather than spill their results.
+instruction-level parallelism; the other collision kernels and collide_ilp3.hip
+sink instructions into the loops where they are used rather than spill their
+results, but for collide_fp64_timed.hip and collide_generic_aux.hip, which run
+faster without.
 """
 from __future__ import annotations
 
@@ -22,9 +23,10 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libmcd.so")
 SOURCES = ["collide_batched.hip", "collide_batched_prob.hip", "collide_fp64.hip",
-           "collide_fp64_timed.hip", "collide_ilp.hip", "collide_ilp3.hip", "collide_plain.hip",
-           "collide_plain_prob.hip", "capi.hip", "collide.hip", "binning.hip", "plan.hip",
-           "transport.hip", "diagnostics.hip", "noalloc.hip"]
+           "collide_fp64_timed.hip", "collide_generic_aux.hip", "collide_ilp.hip",
+           "collide_ilp3.hip", "collide_plain.hip", "collide_plain_prob.hip", "capi.hip",
+           "collide.hip", "binning.hip", "plan.hip", "transport.hip", "diagnostics.hip",
+           "noalloc.hip"]
 # per-file flags on top of CFLAGS
 ILP = ["-mllvm", "--amdgpu-sched-strategy=max-ilp"]
 SINK = ["-mllvm", "-sink-insts-to-avoid-spills=1"]

@@ -8,8 +8,12 @@
 
 namespace mcd {
 
-// defined in collide_ilp.hip, collide_ilp3.hip, collide_fp64.hip and
-// collide_fp64_timed.hip
+// defined in collide_ilp.hip, collide_ilp3.hip, collide_fp64.hip,
+// collide_fp64_timed.hip and collide_generic_aux.hip
+extern template __global__ void collide_batched<float, 4, false, false, true, kEitherLimit>(
+    CollideArgs A);
+extern template __global__ void collide_batched<float, 4, false, true, true, kEitherLimit>(
+    CollideArgs A);
 extern template __global__ void collide_batched<float, 4, true, false, false, kTimeLimited>(
     CollideArgs A);
 extern template __global__ void collide_batched<float, 4, true, false, true, kTimeLimited>(
