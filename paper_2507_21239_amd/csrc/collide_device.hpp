@@ -1270,16 +1270,17 @@ __device__ __forceinline__ void process_cell(const CollideArgs &A, int cell, cha
 // (largest first), each wave popping its own work
 // ---------------------------------------------------------------------------
 //
-// Waves per SIMD the mixed form's registers are limited to: three for fixed
-// counts (every cell a long chain: throughput) and with the composition mix;
-// two for time-limited steps without it, where a few cells' chains or the
-// row-sum builds set the pace and spills cost more than the third wave gives
-// (first steps of a 5e5 disk: 1.76 against 1.85 ms for four; one column: 2.71
-// against 2.77 ms per step; with 8 fractions, 2e6 particles: 5.45 against
-// 5.15 ms, so not there)
+// Waves per SIMD the mixed form's registers are limited to: three, for the
+// throughput of many cells (2500 cells of 64 - 1024 particles, 100 events, test
+// kernel: 1208 against 1678 us with two, Maxwell criterion 1811 against 2171); two
+// for the time-limited steps that have a kernel of their own without the
+// composition mix, where a few cells' chains or the row-sum builds set the pace
+// and spills cost more than the third wave gives (first steps of a 5e5 disk: 1.76
+// against 1.85 ms for four; one column: 2.71 against 2.77 ms per step; with 8
+// fractions, 2e6 particles: 5.45 against 5.15 ms, so not there)
 template <typename RT, bool AUX, int LIMIT>
 constexpr int waves_per_simd() {
-  return sizeof(RT) == 4 && (AUX || LIMIT == kFixedCount) ? 3 : 2;
+  return sizeof(RT) == 4 && (AUX || LIMIT != kTimeLimited) ? 3 : 2;
 }
 
 template <typename RT, int KMAX, bool FAST, bool PROB, bool AUX, int LIMIT = kEitherLimit>
