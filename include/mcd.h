@@ -28,9 +28,9 @@
  *    fixes allocate at that call and free in mcd_free: the gas grid's nodes
  *    (mcd_set_gas_grid) and the snapshot staging (mcd_snapshot, first call
  *    or a larger field set).
- *  - Largest cell: 2048 particles in the mixed form, 1536 in FP64 (the
- *    four-wave team's particle records must fit the 160 KB of LDS); larger
- *    cells are rejected with MCD_EINVAL.
+ *  - Largest cell: 2048 particles in the mixed form, 1536 in FP64 (limits of
+ *    this interface; the particle records of such cells fit the 160 KB of
+ *    LDS); larger cells are rejected with MCD_EINVAL.
  *  - Every function returns an mcd_status; no C++ exception crosses the ABI.
  *    After an error, mcd_last_error(ctx) describes it.  Kernels that detect
  *    an anomaly (a NaN or infinite rate, a non-positive mass or volume) set a

@@ -283,7 +283,7 @@ void carve(mcd_ctx *c) {
 }
 
 // LDS region capacities of the batched (or plain) launch from the largest
-// cell of each list; EINVAL if a region does not fit the LDS
+// cell of each list; EINVAL if one exceeds its limit
 mcd_status set_caps(mcd_ctx *c, int32_t max_big, int32_t max_small, int32_t max_cell) {
   c->max_big = max_big;
   c->max_small = max_small;
@@ -292,9 +292,10 @@ mcd_status set_caps(mcd_ctx *c, int32_t max_big, int32_t max_small, int32_t max_
   if (!lds_caps(c->prm.precision, c->prm.schedule, max_big, max_small, max_cell, c->big_cap,
                 c->small_cap))
     return fail(c, MCD_EINVAL,
-                std::string("largest cell does not fit the 160 KB LDS in this precision (") +
+                std::string("a cell exceeds the limit of this precision (largest ") +
                     std::to_string(max_cell) + " particles; at most " +
-                    std::to_string(f64 ? kMaxCellFp64 : kMaxCell) + ")");
+                    std::to_string(f64 ? kMaxCellFp64 : kMaxCell) + ", on one wave " +
+                    std::to_string(f64 ? kSmallCapFp64 : kSmallLimit) + ")");
   return MCD_OK;
 }
 

@@ -140,7 +140,8 @@ static_assert(region_bytes<float>(kMaxCell, 4) <= 160 * 1024, "FP32 cells of kMa
 hipError_t launch_clear_state(DevState *state, Plan *plan, uint32_t step, hipStream_t s);
 
 // LDS capacities of the collision launch from the largest cell of each list
-// (particles): false if a team's region does not fit the 160 KB of LDS
+// (particles): false if one exceeds the limits above or a team's region the
+// 160 KB of LDS
 inline bool lds_caps(int precision, int schedule, int max_big, int max_small, int max_cell,
                      int &big_cap, int &small_cap) {
   big_cap = max_big > 0 ? (max_big + 255) / 256 * 256 : 0;

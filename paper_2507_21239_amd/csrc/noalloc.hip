@@ -110,7 +110,7 @@ extern "C" mcd_status mcd_collide_noalloc(const mcd_params *params, const mcd_pa
   int big_cap = 0, small_cap = 0;
   if (!lds_caps(precision, schedule, big ? bound : 0, big ? kNoallocSmallMax : bound, bound,
                 big_cap, small_cap))
-    return fail(MCD_EINVAL, "cells of max_cell particles do not fit the 160 KB LDS in this precision"
+    return fail(MCD_EINVAL, "max_cell exceeds the largest cell of this precision"
                             " (at most " + std::to_string(precision == MCD_FP64 ? kMaxCellFp64 : kMaxCell) + ")");
   char *sc = nullptr;
   mcd_status st = scratch_address(&sc);
