@@ -591,7 +591,7 @@ template <typename RT, bool CODE>
 __device__ __forceinline__ int event_outcome(const OutcomeConst &P, bool fast, double mi, double mj,
                                              double u4, double &mnew, OutcomeCounts &n) {
   if constexpr (sizeof(RT) == 8) {
-    const int oc = __builtin_amdgcn_readfirstlane(outcome<true>(P, fast, mi, mj, u4, mnew));
+    const int oc = __builtin_amdgcn_readfirstlane(outcome(P, fast, mi, mj, u4, mnew));
     n.n_fast += oc != OUT_STICK ? 1u : 0u;
     n.n_small += oc == OUT_ERODED_SMALL ? 1u : 0u;
     n.n_frag += oc == OUT_FRAG ? 1u : 0u;

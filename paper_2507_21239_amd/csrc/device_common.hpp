@@ -123,15 +123,6 @@ __device__ inline double dpp_t(double x) {
 
 // inclusive prefix sum over the 64 lanes: shifts of 1, 2, 4, 8 inside rows of
 // 16 lanes, then row broadcasts of lanes 15 and 31 (gfx9 DPP)
-__device__ inline float wave_incl_scan(float x) {
-  x += dpp_f<0x111, 0xf, 0xf>(x);  // row_shr:1
-  x += dpp_f<0x112, 0xf, 0xf>(x);  // row_shr:2
-  x += dpp_f<0x114, 0xf, 0xf>(x);  // row_shr:4
-  x += dpp_f<0x118, 0xf, 0xf>(x);  // row_shr:8
-  x += dpp_f<0x142, 0xa, 0xf>(x);  // row_bcast:15 into rows 1, 3
-  x += dpp_f<0x143, 0xc, 0xf>(x);  // row_bcast:31 into rows 2, 3
-  return x;
-}
 __device__ inline double wave_incl_scan(double x) {
   x += dpp_d<0x111, 0xf, 0xf>(x);  // row_shr:1
   x += dpp_d<0x112, 0xf, 0xf>(x);  // row_shr:2
@@ -176,7 +167,5 @@ __device__ inline double wave_max_nonneg(double x) {
 }
 
 __device__ inline uint64_t ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
-__device__ inline int first_set(uint64_t b) { return b ? __builtin_ctzll(b) : -1; }
-__device__ inline int last_set(uint64_t b) { return b ? 63 - __builtin_clzll(b) : -1; }
 
 }  // namespace mcd

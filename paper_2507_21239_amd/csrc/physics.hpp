@@ -392,12 +392,9 @@ __device__ inline Rec<float> make_rec_f(const CellF &c, double m, float Mn) {
   return r;
 }
 
-// precision-specific division and square root: FP64 correctly rounded;
+// precision-specific square root and the FP32 division: FP64 correctly rounded;
 // FP32 through the hardware reciprocal and square root (about 1 ulp)
-__device__ inline double pdiv(double a, double b) { return a / b; }
 __device__ inline float pdiv(float a, float b) { return a * __builtin_amdgcn_rcpf(b); }
-__device__ inline double prcp(double b) { return 1.0 / b; }
-__device__ inline float prcp(float b) { return __builtin_amdgcn_rcpf(b); }
 __device__ inline double psqrt(double x) { return sqrt(x); }
 __device__ inline float psqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
 
@@ -422,19 +419,20 @@ __device__ inline RT dv2_turb(const PairConst<RT> &c, const Rec<RT> &x, const Re
     const double den = tiny ? sum : inter ? sum * q : fma(St1, k, k) * (1.0 + St2);
     const double rest = inter ? (2.0 * kYa - 1.0) * St1 - St2 : 0.0;
     return c.Vg2 * (rest + num / den);
+  } else {
+    if (St1 < c.St_eta) {
+      const float h1 = xb ? x.h : y.h, h2 = xb ? y.h : x.h;
+      return pdiv(c.Vg2 * (St1 - St2), St1 + St2) * (h1 - h2);
+    }
+    if (St1 < 1.0f) {
+      const float eps = pdiv(St2, St1);
+      const float br = (float)(2.0 * kYa) - (1.0f + eps) +
+                       pdiv(2.0f, 1.0f + eps) *
+                           ((float)(1.0 / (1.0 + kYa)) + pdiv(eps * eps * eps, (float)kYa + eps));
+      return c.Vg2 * St1 * br;
+    }
+    return c.Vg2 * (x.q1 + y.q1);
   }
-  if (St1 < c.St_eta) {
-    const RT h1 = xb ? x.h : y.h, h2 = xb ? y.h : x.h;
-    return pdiv(c.Vg2 * (St1 - St2), St1 + St2) * (h1 - h2);
-  }
-  if (St1 < (RT)1) {
-    const RT eps = pdiv(St2, St1);
-    const RT br = (RT)(2.0 * kYa) - ((RT)1 + eps) +
-                  pdiv((RT)2, (RT)1 + eps) *
-                      ((RT)(1.0 / (1.0 + kYa)) + pdiv(eps * eps * eps, (RT)kYa + eps));
-    return c.Vg2 * St1 * br;
-  }
-  return c.Vg2 * (x.q1 + y.q1);
 }
 
 // relative velocity of the pair (five sources in quadrature)
@@ -619,31 +617,21 @@ __host__ __device__ inline double group_factor(double dm_max, double mi, double 
 }
 
 // collision outcome for representative particle i (mass mi) hitting a body
-// of swarm j (mass mj) at relative velocity dv; returns the outcome code.
-// EXACT: the grouped mass grp * mj and the mass-ratio test as written (the
-// FP64 path); otherwise their division-free equivalents max(mj, dm_max mi)
-// and big >= ratio * small, equal up to one rounding (the mixed path)
-template <bool EXACT = true, typename PP>
+// of swarm j (mass mj) at relative velocity dv, in the FP64 form; returns the
+// outcome code (the mixed form's rules: event_outcome)
+template <typename PP>
 __host__ __device__ inline int outcome(const PP &P, bool fast, double mi, double mj, double u,
                                        double &m_new) {
   // grouped mass grp * mj; the eroded mass chi grp mj
-  double gm, em;
-  if (EXACT) {
-    const double grp = group_factor(P.dm_max, mi, mj);
-    gm = grp * mj;
-    em = P.erosion_chi * grp * mj;
-  } else {
-    const double d = P.dm_max * mi;
-    gm = (P.dm_max > 0.0 && d > mj) ? d : mj;
-    em = P.erosion_chi * gm;
-  }
+  const double grp = group_factor(P.dm_max, mi, mj);
+  const double gm = grp * mj, em = P.erosion_chi * grp * mj;
   if (P.kernel != K_PHYSICAL || !fast) {
     m_new = mi + gm;
     return OUT_STICK;
   }
   const double big = mi > mj ? mi : mj;
   const double small = mi > mj ? mj : mi;
-  if (EXACT ? big / small >= P.erosion_ratio : big >= P.erosion_ratio * small) {
+  if (big / small >= P.erosion_ratio) {
     if (mi >= mj) {
       const double m = mi - em;
       m_new = m > P.m0 ? m : P.m0;
