@@ -53,13 +53,13 @@ EVENTS_PER_CELL = 1000
 # of WRITE_SIZE: factors 2.0 and 1.0).
 # Valid only for the kernel sources it was taken on: their SHA-256 is kept
 # and compared at run time; on any change `traffic` is reported as null.
-TRAFFIC = {"fetch_kib": 17464.625, "write_kib": 13209.594, "fetch_factor": 1.99994, "write_factor": 1.0,
-           "sources_sha256": "9d17beb71946e44263bad25858498783b8736234daba3e4a9f130b2a2e3e7f83"}
+TRAFFIC = {"fetch_kib": 17158.3125, "write_kib": 11673.46875, "fetch_factor": 1.99994, "write_factor": 1.0,
+           "sources_sha256": "b00ccfb121b6f55edea4055de2b0ba94f2aa371ea180b3a5094f49f008f7e933"}
 # Issue rate of the same launch from one `rocprofv3 --pmc` pass of SQ counters:
 # VALU busy = 4 * SQ_ACTIVE_INST_VALU / (1024 SIMDs * launch cycles at 2.4 GHz),
 # and SQ_INSTS_VALU per collision; the same validity rule as TRAFFIC.
-ISSUE = {"valu_busy": 0.900, "valu_insts_per_collision": 1395,
-         "sources_sha256": "9d17beb71946e44263bad25858498783b8736234daba3e4a9f130b2a2e3e7f83"}
+ISSUE = {"valu_busy": 0.875, "valu_insts_per_collision": 1395,
+         "sources_sha256": "b00ccfb121b6f55edea4055de2b0ba94f2aa371ea180b3a5094f49f008f7e933"}
 KERNEL_SOURCES = ("paper_2507_21239_amd/csrc/collide.hip", "paper_2507_21239_amd/csrc/collide_launch.hpp",
                   "paper_2507_21239_amd/csrc/collide_device.hpp", "paper_2507_21239_amd/csrc/collide_ilp3.hip",
                   "paper_2507_21239_amd/csrc/physics.hpp", "paper_2507_21239_amd/csrc/device_common.hpp",

@@ -22,8 +22,8 @@
 // masses and particle indices stay in registers of the owning lane; masses go
 // back to HBM once, when the cell is done.  The starting row sums evaluate each
 // unordered pair once (build_rows_pairwise*) in the FP32 fast path and in FP64,
-// both up to four slots per lane; otherwise every row is summed in canonical
-// order.  The batched kernel carries the composition mix and the event log only
+// both up to four slots per lane; otherwise, and in FP64 teams of few particles,
+// every row is summed in canonical order.  The batched kernel carries the composition mix and the event log only
 // in the variant launched for runs that use them.
 //
 // The cell body and the kernel templates; collide_launch.hpp launches them.
@@ -1172,12 +1172,14 @@ __device__ __forceinline__ void process_cell(const CollideArgs &A, int cell, cha
   team_sync<NW>();
 
   // ---- row sums r_i = sum_k r_ik ------------------------------------------
-  // The FP32 fast path and FP64 up to four slots per lane evaluate each
+  // The FP32 fast path and FP64, up to four slots per lane, evaluate each
   // unordered pair once (build_rows_pairwise, build_rows_pairwise_team; batched
   // FP64 workload, 250 events: 2.72 against 3.35 ms; own slots one after the
-  // other, a quarter of the code: 2.73, its row sums alone 15% slower).  Otherwise partners k = 0..n-1 are read once per
-  // group of G own slots and paired with each of them (independent
-  // evaluations), and each row adds its terms in canonical order.
+  // other, a quarter of the code: 2.73, its row sums alone 15% slower), but for
+  // FP64 teams with few particles (build_rows_plain).  Otherwise partners
+  // k = 0..n-1 are read once per group of G own slots and paired with each of
+  // them (independent evaluations), and each row adds its terms in canonical
+  // order.
   double r[KMAX];
   bool built = false;
   if constexpr ((sizeof(RT) == 8 || FAST) && KMAX == 4) {
